@@ -389,7 +389,9 @@ ks_status ks_simulate(const ks_model* model, const ks_spec* specs, int32_t n_spe
 
 /* Bytes of device workspace ks_eval_kernels / ks_eval_steps / ks_validate
  * need for this record set and spec count (256-byte aligned).  0 on bad
- * arguments. */
+ * arguments.  For large record sets this includes room for their different
+ * records (kernels that recur from layer to layer or step to step with equal
+ * fields), which step sums of MLP heads evaluate once each. */
 size_t ks_workspace_bytes(const ks_desc* desc, int32_t n_specs);
 
 /* Per-pair latencies (Eq. 2) for every spec vector and record.  ws: device

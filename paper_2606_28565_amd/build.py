@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -39,23 +40,23 @@ def _run(cmd):
 
 
 def build(verbose: bool = False) -> str:
-    objs = []
     tmp = os.path.join(PKG, "_obj")
     os.makedirs(tmp, exist_ok=True)
-    kern = os.path.join(tmp, "ks_kernels.o")
-    api = os.path.join(tmp, "ks_api.o")
     common = ["-I", INCLUDE, "-I", CSRC]
-    expand = os.path.join(tmp, "ks_expand.o")
-    _run([HIPCC, *DEVICE_FLAGS, *common, "-c", os.path.join(CSRC, "ks_kernels.hip"), "-o", kern])
-    _run([HIPCC, *DEVICE_FLAGS, *common, "-c", os.path.join(CSRC, "ks_expand.hip"), "-o", expand])
-    static = os.path.join(tmp, "ks_static.o")
-    _run([HIPCC, *DEVICE_FLAGS, *common, "-c", os.path.join(CSRC, "ks_static.hip"), "-o", static])
-    _run([HIPCC, *HOST_FLAGS, *common, "-D__HIP_PLATFORM_AMD__", "-c",
-          os.path.join(CSRC, "ks_api.cpp"), "-o", api])
-    simo = os.path.join(tmp, "ks_sim.o")
-    _run([HIPCC, *HOST_FLAGS, *common, "-D__HIP_PLATFORM_AMD__", "-c",
-          os.path.join(CSRC, "ks_sim.cpp"), "-o", simo])
-    objs = [kern, expand, static, api, simo]
+    jobs = []
+    for src in ("ks_kernels.hip", "ks_unique.hip", "ks_finish.hip", "ks_expand.hip", "ks_static.hip"):
+        jobs.append((src, [HIPCC, *DEVICE_FLAGS, *common]))
+    for src in ("ks_api.cpp", "ks_sim.cpp"):
+        jobs.append((src, [HIPCC, *HOST_FLAGS, *common, "-D__HIP_PLATFORM_AMD__"]))
+
+    def compile_one(job):
+        src, cmd = job
+        obj = os.path.join(tmp, os.path.splitext(src)[0] + ".o")
+        _run([*cmd, "-c", os.path.join(CSRC, src), "-o", obj])
+        return obj
+
+    with ThreadPoolExecutor(max_workers=4) as pool:
+        objs = list(pool.map(compile_one, jobs))
     tmp_lib = LIB + ".tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp_lib])
     os.replace(tmp_lib, LIB)

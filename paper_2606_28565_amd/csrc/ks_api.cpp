@@ -57,9 +57,95 @@ constexpr size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 //   range   : KS_NFAM * n_steps * 2 uint32 per (family, step) record range
 //   partial : KS_NFAM * n_steps * n_specs double (spec-minor)
 //   carry   : n_tiles * n_specs double (spec-minor)
+// and, where the different records are evaluated instead of all (uniq_plan):
+//   ctl     : 256 B, right after range (cleared with it): their count per
+//             family [KS_NFAM] and, at word 15, the flag that they did not fit
+//   rows    : uint32 per table slot: a record's row + 1 (cleared with range)
+//   slot    : uint32 per table slot, after carry: its index
+//   count   : uint32 per chunk: its entries
+//   list    : uint32 per different record: its row
+//   ent     : 8 B per entry, then uint32 per entry: its slot
+//   ut      : n_specs float per different record
 struct Layout {
-  size_t specc, agg, range, partial, carry, total;
+  size_t specc, agg, range, partial, carry, base;   // base: without the different records
+  size_t ctl, rows, slot, count, list, ent, ut, total;     // total = base without them
 };
+
+// The head work of every record from which finding the different ones pays:
+// 20 us at the rate the heads reach on the whole chip (fp32 70 TFLOP/s, bf16
+// 1.2 PFLOP/s).  Below it the two more kernels (8 us each at any size) cost
+// more than the evaluation.
+constexpr double kUniqF32Flops = 1.4e9, kUniqBf16Flops = 2.4e10;
+// (pairs of records and spec vectors that no head turns into that much work)
+constexpr double kUniqPairs = kUniqF32Flops / (2.0 * 128 * (32 + 128));
+
+// The different records of a call: which families, and the room for their
+// entries and records.  A family of at most kFlatPerStep records per step gets
+// room for all of them; a larger one (a record per layer) a quarter of its
+// records as entries and the different records of four kernels per layer, one
+// step at a time, with a margin (when they do not fit, every record is
+// evaluated).  Grouped GEMMs stay out: each layer has its own routed rows.
+constexpr int64_t kFlatPerStep = 8;
+constexpr int kUniqOver = 15;
+
+struct UniqPlan {
+  uint32_t mask = 0;
+  bool may_overflow = false;
+  int32_t chunk_off[KS_NFAM + 1];
+  uint32_t chunk_entries[KS_NFAM], ent_off[KS_NFAM], base[KS_NFAM], cap[KS_NFAM];
+  uint32_t slot_off[KS_NFAM], slots[KS_NFAM], slot_mask[KS_NFAM];
+  int32_t scan_off[KS_NFAM + 1], unit_off[KS_NFAM + 1];
+  uint32_t entries = 0, records = 0, all_slots = 0;
+};
+
+bool uniq_plan(const ks_desc *d, int32_t n_specs, UniqPlan *pl) {
+  if ((double)d->n_rows * n_specs < kUniqPairs) return false;
+  int64_t ent = 0, rec = 0, chunks = 0, slots = 0, scans = 0, units = 0;
+  for (int f = 0; f < KS_NFAM; ++f) {
+    const int64_t rows = f == KS_GROUPED_GEMM ? 0 : d->fam_off[f + 1] - d->fam_off[f];
+    const bool flat = rows <= kFlatPerStep * d->n_steps;
+    const int64_t n = (rows + ks::kUniqChunk - 1) / ks::kUniqChunk;
+    const int64_t room = 4 * d->n_steps + rows / 32 + 64;
+    pl->chunk_off[f] = (int32_t)chunks;
+    pl->ent_off[f] = (uint32_t)ent;
+    pl->base[f] = (uint32_t)rec;
+    pl->chunk_entries[f] = flat ? ks::kUniqChunk : ks::kUniqChunk / 4;
+    pl->cap[f] = (uint32_t)(flat || rows < room ? rows : room);
+    if (rows > 0) pl->mask |= 1u << f;
+    pl->may_overflow = pl->may_overflow || !flat;
+    // the table: a slot per step for attention; for a dense family twice its
+    // records, up to 2^15 (GEMMs, several kernels per layer, 2^18): a trace's
+    // token counts are a few thousand, and a slot taken by another record
+    // costs one more evaluation
+    int64_t ns = 0;
+    if (f == KS_ATTN_PREFILL || f == KS_ATTN_DECODE) {
+      ns = rows > 0 ? d->n_steps : 0;
+    } else if (rows > 0) {
+      ns = 256;
+      while (ns < (f == KS_GEMM ? int64_t(1) << 18 : int64_t(1) << 15) && ns < 2 * rows) ns *= 2;
+    }
+    pl->slot_off[f] = (uint32_t)slots;
+    pl->slots[f] = (uint32_t)ns;
+    pl->slot_mask[f] = (uint32_t)(ns > 0 ? ns - 1 : 0);
+    pl->scan_off[f] = (int32_t)scans;
+    pl->unit_off[f] = (int32_t)units;
+    slots += ns;
+    scans += (ns + ks::kUniqScan - 1) / ks::kUniqScan;
+    units += flat ? 4 * n : n;
+    if (slots >= (int64_t(1) << 30)) return false;
+    chunks += n;
+    ent += n * pl->chunk_entries[f];
+    rec += pl->cap[f];
+    if (ent >= (int64_t(1) << 30) || rec >= (int64_t(1) << 30)) return false;
+  }
+  pl->chunk_off[KS_NFAM] = (int32_t)chunks;
+  pl->entries = (uint32_t)ent;
+  pl->records = (uint32_t)rec;
+  pl->scan_off[KS_NFAM] = (int32_t)scans;
+  pl->unit_off[KS_NFAM] = (int32_t)units;
+  pl->all_slots = (uint32_t)slots;
+  return pl->mask != 0;
+}
 
 struct Tiles {
   int32_t tile_off[KS_NFAM + 1];
@@ -78,10 +164,12 @@ Tiles tiles_of(const ks_desc *d) {
   return t;
 }
 
-Layout layout_of(const ks_desc *d, int32_t n_specs) {
+// pl: room for the different records too (nullptr: not)
+Layout layout_of(const ks_desc *d, int32_t n_specs, const UniqPlan *pl = nullptr) {
   const Tiles t = tiles_of(d);
   const size_t S = (size_t)d->n_steps;
   Layout L;
+  std::memset(&L, 0, sizeof L);
   size_t off = 256;
   L.specc = off;
   off += align256((size_t)n_specs * sizeof(ks::SpecC));
@@ -89,10 +177,30 @@ Layout layout_of(const ks_desc *d, int32_t n_specs) {
   off += align256(4 * S * sizeof(uint64_t));
   L.range = off;
   off += align256((size_t)KS_NFAM * S * 2 * sizeof(uint32_t));
+  const size_t before = off;
+  if (pl) {
+    L.ctl = off;
+    L.rows = off + 256;
+    off += 256 + align256((size_t)pl->all_slots * sizeof(uint32_t));
+  }
+  const size_t extra = off - before;
   L.partial = off;
   off += align256((size_t)n_specs * KS_NFAM * S * sizeof(double));
   L.carry = off;
   off += align256((size_t)n_specs * (size_t)t.tile_off[KS_NFAM] * sizeof(double));
+  L.base = off - extra;
+  if (pl) {
+    L.slot = off;
+    off += align256((size_t)pl->all_slots * sizeof(uint32_t));
+    L.count = off;
+    off += align256((size_t)pl->chunk_off[KS_NFAM] * sizeof(uint32_t));
+    L.list = off;
+    off += align256((size_t)pl->records * sizeof(uint32_t));
+    L.ent = off;
+    off += align256((size_t)pl->entries * (sizeof(ks::UniqEntry) + sizeof(uint32_t)));
+    L.ut = off;
+    off += align256((size_t)pl->records * (size_t)n_specs * sizeof(float));
+  }
   L.total = off;
   return L;
 }
@@ -182,8 +290,8 @@ ks_status check_common(const ks_desc *d, const ks_spec *specs, int32_t n_specs, 
   if (!specs) return fail(KS_EINVAL, "specs is NULL");
   *L = layout_of(d, n_specs);
   if (!ws) return fail(KS_EWORKSPACE, "workspace is NULL");
-  if (ws_bytes < L->total)
-    return fail(KS_EWORKSPACE, "workspace %zu bytes < %zu required", ws_bytes, L->total);
+  if (ws_bytes < L->base)
+    return fail(KS_EWORKSPACE, "workspace %zu bytes < %zu required", ws_bytes, L->base);
   if (reinterpret_cast<uintptr_t>(ws) % 256)
     return fail(KS_EWORKSPACE, "workspace not 256-byte aligned");
   return KS_OK;
@@ -246,12 +354,80 @@ void fill_eval(ks::EvalParams &p, const ks_desc *d, const ks_spec *specs, int32_
   p.err = reinterpret_cast<uint32_t *>(ws);
 }
 
+// Whether a call evaluates only its different records: step sums of MLP heads
+// without per-pair outputs, given the workspace for it, and enough head work.
+bool takes_uniq(const ks_desc *d, int32_t n_specs, const ks_heads *h, int kind, const ks_kernel_out *kout,
+                size_t ws_bytes, UniqPlan *pl, Layout *L) {
+  if (kind == ks::kEtaOne || kind == ks::kBoundedOnly || d->n_rows == 0) return false;
+  if (kout && (kout->flops || kout->bytes || kout->blocks || kout->t_roof || kout->eta || kout->t_kernel || kout->source))
+    return false;
+  const double flops = 2.0 * (double)d->n_rows * n_specs * h->hidden * (h->in_dim + h->hidden);
+  if (flops < (h->precision == KS_F32 ? kUniqF32Flops : kUniqBf16Flops)) return false;
+  if (!uniq_plan(d, n_specs, pl)) return false;
+  const Layout full = layout_of(d, n_specs, pl);
+  if (ws_bytes < full.total) return false;
+  *L = full;
+  return true;
+}
+
+void fill_uniq(ks::UniqParams &u, ks::EvalParams &p, const ks_desc *d, const UniqPlan &pl, char *ws, const Layout &L) {
+  std::memset(&u, 0, sizeof u);
+  u.step = p.step;
+  u.m = p.m;
+  u.n = p.n;
+  u.k = p.k;
+  u.a = p.a;
+  u.mult = p.mult;
+  u.n_steps = p.n_steps;
+  u.may_overflow = pl.may_overflow;
+  u.ent = reinterpret_cast<ks::UniqEntry *>(ws + L.ent);
+  u.dir = reinterpret_cast<uint32_t *>(ws + L.range);
+  u.list = reinterpret_cast<uint32_t *>(ws + L.list);
+  u.count = reinterpret_cast<uint32_t *>(ws + L.ctl);
+  u.over = u.count + kUniqOver;
+  u.chunk_count = reinterpret_cast<uint32_t *>(ws + L.count);
+  u.slot_row = reinterpret_cast<uint32_t *>(ws + L.rows);
+  u.slot_id = reinterpret_cast<uint32_t *>(ws + L.slot);
+  u.ent_slot = reinterpret_cast<uint32_t *>(u.ent + pl.entries);
+  u.req_off = d->req_off;
+  u.req_q = d->req_q;
+  u.req_h = d->req_h;
+  u.n_req = d->n_req;
+  u.agg = reinterpret_cast<uint64_t *>(ws + L.agg);
+  u.err = p.err;
+  p.uniq_mask = pl.mask;
+  p.u_list = u.list;
+  p.u_count = u.count;
+  p.u_over = u.over;
+  p.u_t = reinterpret_cast<float *>(ws + L.ut);
+  for (int f = 0; f < KS_NFAM; ++f) {
+    u.fam_off[f] = p.fam_off[f];
+    u.chunk_off[f] = pl.chunk_off[f];
+    u.chunk_entries[f] = pl.chunk_entries[f];
+    u.ent_off[f] = pl.ent_off[f];
+    u.slot_off[f] = pl.slot_off[f];
+    u.slots[f] = pl.slots[f];
+    u.slot_mask[f] = pl.slot_mask[f];
+    u.scan_off[f] = pl.scan_off[f];
+    u.unit_off[f] = pl.unit_off[f];
+    u.base[f] = p.u_base[f] = pl.base[f];
+    u.cap[f] = p.u_cap[f] = pl.cap[f];
+  }
+  u.fam_off[KS_NFAM] = p.fam_off[KS_NFAM];
+  u.chunk_off[KS_NFAM] = pl.chunk_off[KS_NFAM];
+  u.scan_off[KS_NFAM] = pl.scan_off[KS_NFAM];
+  u.unit_off[KS_NFAM] = pl.unit_off[KS_NFAM];
+}
+
 ks_status prologue(const ks_desc *d, const ks_spec *specs, int32_t n_specs, char *ws, const Layout &L,
-                   bool with_range, hipStream_t s) {
+                   bool with_range, hipStream_t s, bool uniq = false) {
+  // (with the different records, their counts and table follow the ranges)
+  const int64_t clear = uniq ? (int64_t)(L.partial - L.range) / 4 : with_range ? 2 * (int64_t)KS_NFAM * d->n_steps : 0;
   hipError_t e = ks::launch_clear_prep(reinterpret_cast<uint32_t *>(ws), reinterpret_cast<uint32_t *>(ws + L.range),
-                                       with_range ? 2 * (int64_t)KS_NFAM * d->n_steps : 0, specs, n_specs,
+                                       clear, specs, n_specs,
                                        reinterpret_cast<ks::SpecC *>(ws + L.specc), s);
   if (e != hipSuccess) return hip_fail(e, "clear and spec constants launch");
+  if (uniq) return KS_OK;   // the request sums are formed beside the first of their kernels
   e = ks::launch_attn_agg(d->req_off, d->req_q, d->req_h, d->n_steps, d->n_req,
                           reinterpret_cast<uint64_t *>(ws + L.agg), reinterpret_cast<uint32_t *>(ws), s);
   if (e != hipSuccess) return hip_fail(e, "attention aggregate launch");
@@ -410,7 +586,8 @@ extern "C" {
 
 size_t ks_workspace_bytes(const ks_desc *desc, int32_t n_specs) {
   if (check_desc(desc) != KS_OK || n_specs < 1 || n_specs > (1 << 20)) return 0;
-  return layout_of(desc, n_specs).total;
+  UniqPlan pl;
+  return layout_of(desc, n_specs, uniq_plan(desc, n_specs, &pl) ? &pl : nullptr).total;
 }
 
 ks_status ks_eval_kernels(const ks_desc *desc, const ks_spec *specs, int32_t n_specs, const ks_heads *heads,
@@ -452,10 +629,17 @@ static ks_status eval_steps_impl(const ks_desc *desc, const ks_steps *steps, con
   if (!out || (desc->n_steps > 0 && (!out->t_body || !out->t_gpu || !out->t_step)))
     return fail(KS_EINVAL, "a step output is NULL");
   char *w = static_cast<char *>(ws);
-  st = prologue(desc, specs, n_specs, w, L, true, stream);
+  UniqPlan pl;
+  const bool uniq = takes_uniq(desc, n_specs, heads, kind, kout, ws_bytes, &pl, &L);
+  st = prologue(desc, specs, n_specs, w, L, true, stream, uniq);
   if (st != KS_OK) return st;
   ks::EvalParams p;
   fill_eval(p, desc, specs, n_specs, heads, kout, w, L);
+  ks::UniqParams u;
+  if (uniq) {
+    fill_uniq(u, p, desc, pl, w, L);
+    p.uniq = &u;
+  }
   p.partial = reinterpret_cast<double *>(w + L.partial);
   p.carry = reinterpret_cast<double *>(w + L.carry);
   p.range = reinterpret_cast<uint32_t *>(w + L.range);
@@ -481,6 +665,20 @@ static ks_status eval_steps_impl(const ks_desc *desc, const ks_steps *steps, con
   f.carry = p.carry;
   f.n_tiles = p.n_tiles;
   f.range = p.range;
+  if (uniq) {
+    f.uniq_mask = pl.mask;
+    f.u_over = u.over;
+    f.u_ent = u.ent;
+    f.u_slot = u.slot_id;
+    f.u_t = p.u_t;
+    for (int i = 0; i < KS_NFAM; ++i) {
+      f.u_chunk_entries[i] = pl.chunk_entries[i];
+      f.u_ent_off[i] = pl.ent_off[i];
+    }
+    f.u_ent_end = pl.entries;
+    f.u_slots = pl.all_slots;
+    f.u_total = pl.records;
+  }
   f.host = *host;
   f.t_body = out->t_body;
   f.t_gpu = out->t_gpu;

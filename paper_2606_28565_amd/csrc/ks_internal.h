@@ -46,6 +46,43 @@ struct alignas(16) SpecC {
 };
 static_assert(sizeof(SpecC) == 64, "SpecC is one 64-byte record");
 
+// ---- the different records of a call
+constexpr int kUniqChunk = 1024;               // records per workgroup of k_unique
+constexpr uint32_t kUniqScan = 4096;           // slots per workgroup of k_join
+constexpr uint32_t kUniqSlot = 1u << 30;       // an entry's id: a slot (else an index of the different records)
+constexpr uint32_t kUniqIndex = kUniqSlot - 1;
+constexpr uint32_t kUniqNone = 0xFFFFFFFFu;    // no record (its step is out of range)
+
+struct UniqEntry {
+  uint32_t id;    // its row from k_unique, its id from k_join
+  float weight;   // how many dispatches of the step it stands for; sign bit: the last of its piece
+};
+
+struct UniqParams {
+  const uint32_t *step, *m, *n, *k, *a, *mult;   // mult nullable
+  int64_t n_steps;
+  int64_t fam_off[KS_NFAM + 1];
+  int32_t chunk_off[KS_NFAM + 1];      // chunks of the families taken (none for the others)
+  uint32_t chunk_entries[KS_NFAM];     // entry slots of a chunk
+  uint32_t ent_off[KS_NFAM];           // a family's first entry
+  uint32_t base[KS_NFAM], cap[KS_NFAM];
+  uint32_t slot_off[KS_NFAM], slots[KS_NFAM], slot_mask[KS_NFAM];   // a family's table (attention: a slot per step)
+  int32_t scan_off[KS_NFAM + 1], unit_off[KS_NFAM + 1];              // k_join's workgroups and waves
+  bool may_overflow;                   // host only: the entries or records of some family might not fit
+  UniqEntry *ent;
+  uint32_t *dir;        // [KS_NFAM][n_steps][2]: first entry + 1, end row (zero: no such records)
+  uint32_t *list, *count, *over;
+  uint32_t *chunk_count;   // entries of each chunk
+  uint32_t *slot_row;      // a slot's record: row + 1, or 0
+  uint32_t *slot_id;       // ... and its index among the different records
+  uint32_t *ent_slot;      // an entry's slot
+  // the per-step request sums, formed beside k_unique
+  const uint32_t *req_off, *req_q, *req_h;
+  int64_t n_req;
+  uint64_t *agg;
+  uint32_t *err;
+};
+
 struct EvalParams {
   // records
   const uint32_t *step, *m, *n, *k, *a, *b;
@@ -81,6 +118,16 @@ struct EvalParams {
   double *carry;     // [n_tiles][n_specs]
   uint32_t *range;   // [KS_NFAM][n_steps][2] record range of each (family, step); nullable
   uint32_t *err;
+  // the different records (k_unique), for the families of uniq_mask: k_eval's
+  // unique-record variant evaluates u_list[u_base[f] + i], i < u_count[f], and
+  // stores t at u_t[(u_base[f] + i) n_specs + spec].  u_over (nullable): nonzero
+  // when they did not fit; that variant then does nothing, and a direct launch
+  // that has the pointer runs only then.
+  const UniqParams *uniq;      // host pointer, read by launch_eval only (nullptr: every record is evaluated)
+  uint32_t uniq_mask;
+  const uint32_t *u_list, *u_count, *u_over;
+  uint32_t u_base[KS_NFAM], u_cap[KS_NFAM];
+  float *u_t;
   uint8_t *o_src;    // per pair: 0 head of the mode, 1 bounded head, 2 grid (nullable)
 };
 
@@ -96,6 +143,15 @@ struct FinishParams {
   const double *partial, *carry;       // [KS_NFAM][n_steps][n_specs], [n_tiles][n_specs]
   int32_t n_tiles;
   const uint32_t *range;               // [KS_NFAM][n_steps][2]
+  // the different records (uniq_mask 0: none): see EvalParams and UniqParams
+  uint32_t uniq_mask;
+  const uint32_t *u_over;
+  const UniqEntry *u_ent;
+  const uint32_t *u_slot;
+  const float *u_t;
+  uint32_t u_chunk_entries[KS_NFAM], u_ent_off[KS_NFAM];
+  uint32_t u_ent_end;                  // entries in all
+  uint32_t u_slots, u_total;           // slots, different records at most
   ks_host host;
   double *t_body, *t_gpu, *t_step;
   // optional: lat[j] = t_step of step j under spec own[j] (both or neither)
@@ -188,6 +244,10 @@ hipError_t launch_clear_prep(uint32_t *err, uint32_t *range, int64_t n_range, co
 hipError_t launch_attn_agg(const uint32_t *req_off, const uint32_t *q, const uint32_t *h,
                            int64_t n_steps, int64_t n_req, uint64_t *agg, uint32_t *err,
                            hipStream_t s);
+// k_unique and k_join
+hipError_t launch_unique(const UniqParams &p, hipStream_t s);
+// the evaluation of a kind's records; with p.uniq, through the different
+// records of its families
 hipError_t launch_eval(int kind, const EvalParams &p, hipStream_t s);
 hipError_t launch_finish(const FinishParams &p, hipStream_t s);
 // per-pair eta source of a call without a grid (p.o_src, families' bounded bit)

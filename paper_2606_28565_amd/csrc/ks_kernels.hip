@@ -21,6 +21,7 @@
 #include <atomic>
 #include <utility>
 
+#include "ks_agg.h"
 #include "ks_internal.h"
 
 namespace ks {
@@ -98,45 +99,11 @@ __global__ void k_clear(uint32_t *err, uint32_t *range, int64_t n_range, const k
   for (int64_t i = i0; i < n_range; i += (int64_t)gridDim.x * blockDim.x) range[i] = 0;
 }
 
-// Per step j: over its requests r, Q = sum q, KV = sum (h + q),
-// PAIRS = sum (q h + q (q + 1) / 2), TILES = sum ceil(q / 128).  A group of
-// 16 lanes per step strides over its requests, then a butterfly reduction
-// within the group.
-constexpr int kAggLanes = 16;
-
 __global__ void k_attn_agg(const uint32_t *__restrict__ req_off, const uint32_t *__restrict__ rq,
                            const uint32_t *__restrict__ rh, int64_t n_steps, int64_t n_req,
                            uint64_t *__restrict__ agg, uint32_t *err) {
-  const int sub = threadIdx.x & (kAggLanes - 1);
-  const int64_t groups = ((int64_t)gridDim.x * blockDim.x) / kAggLanes;
-  for (int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kAggLanes; j < n_steps; j += groups) {
-    uint32_t r0 = req_off[j], r1 = req_off[j + 1];
-    if (r0 > r1 || (int64_t)r1 > n_req) {
-      if (sub == 0) atomicOr(err, kErrReq);
-      r0 = r1 = 0;
-    }
-    uint64_t Q = 0, KV = 0, P = 0, T = 0;
-    for (uint32_t r = r0 + sub; r < r1; r += kAggLanes) {
-      const uint64_t q = rq[r], h = rh[r];
-      Q += q;
-      KV += h + q;
-      P += q * h + ((q * (q + 1)) >> 1);
-      T += (q + 127) >> 7;
-    }
-#pragma unroll
-    for (int off = kAggLanes / 2; off > 0; off >>= 1) {
-      Q += __shfl_xor(Q, off);
-      KV += __shfl_xor(KV, off);
-      P += __shfl_xor(P, off);
-      T += __shfl_xor(T, off);
-    }
-    if (sub == 0) {
-      agg[j] = Q;
-      agg[n_steps + j] = KV;
-      agg[2 * n_steps + j] = P;
-      agg[3 * n_steps + j] = T;
-    }
-  }
+  attn_agg(req_off, rq, rh, n_steps, n_req, agg, err, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
+           (int64_t)gridDim.x * blockDim.x);
 }
 
 // ------------------------------------------------------------ record counts
@@ -1379,20 +1346,86 @@ __device__ __forceinline__ void tile_edges(const Tile &t, const Fields &f, uint3
 
 // Variants, each a separate instantiation so that the kernels without them
 // keep their registers and schedule: kVarGrid compiles Tier B routing in,
-// kVarMult weights each record's step-sum term by its multiplicity.
-enum : int { kVarGrid = 1, kVarMult = 2, kNumVars = 4 };
+// kVarMult weights each record's step-sum term by its multiplicity, kVarUniq
+// takes the different records k_unique found instead of all of them and
+// stores each one's t for every spec (no step sums, no per-pair outputs).
+enum : int { kVarGrid = 1, kVarMult = 2, kVarUniq = 4, kNumVars = 8 };
 
 // heads that take the software-pipelined spec loop
 template <class H, class = void> struct PipeOK : std::false_type {};
 template <class H> struct PipeOK<H, std::enable_if_t<H::kPipe>> : std::true_type {};
 
+// k_eval over the different records: their tiles per family (counted by
+// k_unique, so known on the device only) and the split of the spec loop that
+// fills the grid when the tiles alone do not.
+struct UniqTiles {
+  int wgt[KS_NFAM + 1], cnt[KS_NFAM];
+  int spec_chunk, n_chunks;
+};
+
+__device__ __forceinline__ void uniq_tiles(const EvalParams &p, int grid, UniqTiles &u) {
+  u.wgt[0] = 0;
+  for (int f = 0; f < KS_NFAM; ++f) {
+    const int c = (p.uniq_mask >> f) & 1u ? (int)min(p.u_count[f], p.u_cap[f]) : 0;
+    u.cnt[f] = c;
+    u.wgt[f + 1] = u.wgt[f] + (c + kWgRows - 1) / kWgRows;
+  }
+  const int n = u.wgt[KS_NFAM];
+  u.spec_chunk = p.n_specs;
+  u.n_chunks = 1;
+  if (n > 0 && n < grid && p.n_specs > 1) {
+    const int chunks = min(max(grid / n, 1), p.n_specs);   // one item per workgroup, never a second round
+    u.spec_chunk = (p.n_specs + chunks - 1) / chunks;
+    u.n_chunks = (p.n_specs + u.spec_chunk - 1) / u.spec_chunk;
+  }
+}
+
+// tile wt of the different records: row0 counts them from the family's first
+__device__ __forceinline__ Tile locate_uniq(const UniqTiles &u, int wt, int wave, int fam0) {
+  Tile t;
+  int fam = fam0;
+  while (wt >= __builtin_amdgcn_readfirstlane(u.wgt[fam + 1])) ++fam;
+  t.fam = fam;
+  t.tile_in_fam = (wt - __builtin_amdgcn_readfirstlane(u.wgt[fam])) * kWgWaves + wave;
+  t.fam_lo = 0;
+  t.fam_hi = __builtin_amdgcn_readfirstlane(u.cnt[fam]);
+  t.row0 = (int64_t)t.tile_in_fam * kTileRows;
+  const int64_t left = t.fam_hi - t.row0;
+  t.nvalid = left <= 0 ? 0 : (left < kTileRows ? (int)left : kTileRows);
+  return t;
+}
+
+__device__ __forceinline__ Fields load_uniq(const EvalParams &p, const Tile &t, int lane) {
+  Fields f = {0, 0, 0, 0, 0, 0, kNoKey, kNoKey, kNoKey, 1.0f};
+  if (t.nvalid == 0) return f;
+  const uint32_t off = (uint32_t)(lane < t.nvalid ? lane : 0);
+  const size_t row = (p.u_list + p.u_base[t.fam] + t.row0)[off];
+  const int fam = t.fam;
+  const bool attn = fam == KS_ATTN_PREFILL || fam == KS_ATTN_DECODE;
+  f.n = p.n[row];
+  if (attn) {
+    f.st = p.step[row];   // (the other families' latency does not depend on the step)
+    f.a = p.a[row];
+  } else {
+    f.m = p.m[row];
+  }
+  if (fam != KS_RMSNORM && fam != KS_SILU_MUL && fam != KS_EMBED) f.k = p.k[row];
+  return f;
+}
+
 // Spec s's per-pair outputs of the lane's record and its segmented step sum:
 // a tail lane stores its segment's sum to dst[s] (dst: the tile's carry
 // slots or the (family, step) partials, one per spec, contiguous), a record
 // of multiplicity m adding m t (one fp32 rounding).
-template <bool MULT>
+// (UNIQ: the record's t to u_dst[s] instead.)
+template <bool MULT, bool UNIQ>
 __device__ __forceinline__ void spec_tail(const EvalParams &p, int s, float t_roof, float eta, float t, bool valid,
-                                          bool live, int64_t row, float tfac, const float (&fac)[6], double *dst) {
+                                          bool live, int64_t row, float tfac, const float (&fac)[6], double *dst,
+                                          float *u_dst) {
+  if constexpr (UNIQ) {
+    if (valid) u_dst[s] = t;
+    return;
+  }
   // (the per-pair test first: a call without per-pair outputs forms no
   // address)
   if ((p.o_troof || p.o_eta || p.o_t) && valid) {
@@ -1425,6 +1458,7 @@ template <int KIND, int VAR>
 __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalParams p) {
   constexpr bool GRID = (VAR & kVarGrid) != 0;
   constexpr bool MULT = (VAR & kVarMult) != 0;
+  constexpr bool UNIQ = (VAR & kVarUniq) != 0;
   using H = typename KindOf<KIND>::H;
   constexpr int IN = KindOf<KIND>::IN;
   __shared__ __align__(16) uint32_t lds[H::LDS_DW];   // 16-byte fragment reads, 8-byte staging writes
@@ -1432,18 +1466,38 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
   __shared__ float grid_lds[KS_GRID_MAX_NODES];   // the staged family's measured grid
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // work item w: workgroup tile w / n_chunks, specs [s0, s1) of range w % n_chunks
-  const int n_chunks = p.n_chunks;
-  const int n_work = p.wgt_off[KS_NFAM] * n_chunks;
-  int staged = -1;
-  // the next tile's fields are loaded while the current one is evaluated
-  Tile tn = {};
-  Fields fn = {0, 0, 0, 0, 0, 0, kNoKey, kNoKey, kNoKey, 1.0f};
+  int n_chunks = p.n_chunks, spec_chunk = p.spec_chunk;
+  int n_wgt = p.wgt_off[KS_NFAM];
+  __shared__ UniqTiles ut;
+  if constexpr (UNIQ) {
+    if (p.u_over[0]) return;   // the records did not fit: the direct launch takes them
+    if (threadIdx.x == 0) uniq_tiles(p, (int)gridDim.x, ut);
+    __syncthreads();
+    n_chunks = __builtin_amdgcn_readfirstlane(ut.n_chunks);
+    spec_chunk = __builtin_amdgcn_readfirstlane(ut.spec_chunk);
+    n_wgt = __builtin_amdgcn_readfirstlane(ut.wgt[KS_NFAM]);
+  } else if (p.u_over) {
+    if (!p.u_over[0]) return;   // the different records were evaluated instead
+  }
+  const int n_work = n_wgt * n_chunks;
   // tiles without a head, and the heads that run one wave per SIMD, take
   // their neighbour steps by a vector load (the scalar loads' round trip is
   // waited for by the next scalar or LDS wait, which one wave per SIMD
   // cannot cover; with two waves per SIMD the vector load measured no
   // better overall)
   constexpr bool VEC = !H::kMlp || MinWg<KIND>::value == 1;
+  auto find = [&](int w, int fam0) {
+    if constexpr (UNIQ) return locate_uniq(ut, item_tile(w, n_chunks), wave, fam0);
+    else return locate(p, item_tile(w, n_chunks), wave, fam0);
+  };
+  auto fetch = [&](const Tile &t) {
+    if constexpr (UNIQ) return load_uniq(p, t, lane);
+    else return load_fields<MULT, VEC>(p, t, lane);
+  };
+  int staged = -1;
+  // the next tile's fields are loaded while the current one is evaluated
+  Tile tn = {};
+  Fields fn = {0, 0, 0, 0, 0, 0, kNoKey, kNoKey, kNoKey, 1.0f};
   // With few work items per workgroup the heads take a contiguous range of
   // them, so that a workgroup meets one or two families and stages their
   // weights into LDS once or twice (striding over the grid it restaged them
@@ -1460,18 +1514,18 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
       blocked ? __builtin_amdgcn_readfirstlane(w_begin + n_work / G + (b < n_work % G ? 1 : 0)) : n_work;
   const int w_step = blocked ? 1 : G;
   if (w_begin < w_end) {
-    tn = locate(p, item_tile(w_begin, n_chunks), wave, 0);
-    fn = load_fields<MULT, VEC>(p, tn, lane);
+    tn = find(w_begin, 0);
+    fn = fetch(tn);
   }
   for (int w = w_begin; w < w_end; w += w_step) {
     const Tile tc = tn;
     const Fields fc = fn;
     if (w + w_step < w_end) {
-      tn = locate(p, item_tile(w + w_step, n_chunks), wave, tc.fam);
-      fn = load_fields<MULT, VEC>(p, tn, lane);
+      tn = find(w + w_step, tc.fam);
+      fn = fetch(tn);
     }
-    const int s_lo = item_range(w, n_chunks) * p.spec_chunk;
-    const int s_hi = min(s_lo + p.spec_chunk, p.n_specs);
+    const int s_lo = item_range(w, n_chunks) * spec_chunk;
+    const int s_hi = min(s_lo + spec_chunk, p.n_specs);
     const int fam = tc.fam;
     // this family takes the bounded head (the plain eta = 1 stream has none)
     const bool bnd = KIND != kEtaOne && ((p.bounded_mask >> fam) & 1u);
@@ -1506,12 +1560,12 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
     // written: no 64-bit products or 64-bit to float conversions.  Calls
     // with a measured grid keep the exact path, so that a record's cell is
     // the one the exact features give.
-    if (!GRID && !p.o_flops && !p.o_bytes && !p.o_blocks) {
+    if (!GRID && (UNIQ || (!p.o_flops && !p.o_bytes && !p.o_blocks))) {
       const CntF cf = record_counts_f(fam, fc.m, fc.n, fc.k, fc.a, fc.b, fc.st, p, bad);
       rc = row_consts(cf.B, cf.F, cf.Bt, cf.M, fc.n, fc.k);
     } else {
       const Cnt c = record_counts(fam, fc.m, fc.n, fc.k, fc.a, fc.b, fc.st, p, bad);
-      if (valid) {
+      if (!UNIQ && valid) {
         if (p.o_flops) p.o_flops[row] = c.F;
         if (p.o_bytes) p.o_bytes[row] = c.Bt;
         if (p.o_blocks) p.o_blocks[row] = c.B;
@@ -1522,44 +1576,50 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
     const bool live = valid && !(bad & kErrStep);
     const bool small = __ballot(rc.B >= kSmallB) == 0;   // wave-uniform
 
-    // segment structure of this tile (spec-independent): keys are sorted
-    const uint32_t key = live ? fc.st : kNoKey;
-    const uint32_t key_dn = dpp_key<0x130, 0xf, 0xf>(key);   // wave_shl:1, lane 63: unequal
-    const bool is_tail = live && key_dn != key;
-    const uint32_t key0 = __builtin_amdgcn_readfirstlane(key);
-    uint32_t prev, next;
-    tile_edges<VEC>(tc, fc, prev, next);
-    const bool to_carry = is_tail && key == key0 && prev == key0;
-    const int tile_id = p.tile_off[fam] + tc.tile_in_fam;
-    if (p.range) {
-      // the (family, step) record range, written where its global first
-      // and last records are
-      const uint32_t key_up = dpp_key<0x138, 0xf, 0xf>(key);   // wave_shr:1
-      const bool head = live && (lane == 0 ? prev != key : key_up != key);
-      const bool tail = live && (lane == nvalid - 1 ? next != key : key_dn != key);
-      if (head) p.range[2 * ((size_t)fam * p.n_steps + key)] = (uint32_t)row;
-      if (tail) p.range[2 * ((size_t)fam * p.n_steps + key) + 1] = (uint32_t)(row + 1);
-    }
-    // A tail lane stores its segment's sum (seg_scan): into the tile's carry
-    // slot if the segment continues from the previous tile, else into the
-    // (spec, family, step) partial.
     float fac[6];
-    seg_factors(key, fac);
-    // the scan input is m t for a live record of multiplicity m (1 without
-    // a multiplicity array) and 0 otherwise: one product per spec instead
-    // of a select.  A lane that is not live either repeats lane 0's record
-    // (a tail lane past nvalid, whose t is finite whenever lane 0's is) or
-    // is flagged bad data; both sit at or after the wave's last live lane or
-    // carry a flagged record, so the scan of every live segment is unchanged.
-    const float tfac = MULT ? (live ? fc.mult : 0.0f) : 0.0f;
-    // (spec-minor layout: a tail lane's sums for all specs are one
-    // contiguous run, so its stores fill whole cache lines)
+    float tfac = 0.0f;
     double *dst = nullptr;
-    if (p.partial && is_tail) {
-      if (to_carry)
-        dst = p.carry + (size_t)tile_id * (size_t)p.n_specs;
-      else
-        dst = p.partial + ((size_t)fam * (size_t)p.n_steps + key) * (size_t)p.n_specs;
+    float *u_dst = nullptr;
+    if constexpr (UNIQ) {
+      u_dst = p.u_t + ((size_t)p.u_base[fam] + (size_t)tc.row0 + (size_t)(valid ? lane : 0)) * (size_t)p.n_specs;
+    } else {
+      // segment structure of this tile (spec-independent): keys are sorted
+      const uint32_t key = live ? fc.st : kNoKey;
+      const uint32_t key_dn = dpp_key<0x130, 0xf, 0xf>(key);   // wave_shl:1, lane 63: unequal
+      const bool is_tail = live && key_dn != key;
+      const uint32_t key0 = __builtin_amdgcn_readfirstlane(key);
+      uint32_t prev, next;
+      tile_edges<VEC>(tc, fc, prev, next);
+      const bool to_carry = is_tail && key == key0 && prev == key0;
+      const int tile_id = p.tile_off[fam] + tc.tile_in_fam;
+      if (p.range) {
+        // the (family, step) record range, written where its global first
+        // and last records are
+        const uint32_t key_up = dpp_key<0x138, 0xf, 0xf>(key);   // wave_shr:1
+        const bool head = live && (lane == 0 ? prev != key : key_up != key);
+        const bool tail = live && (lane == nvalid - 1 ? next != key : key_dn != key);
+        if (head) p.range[2 * ((size_t)fam * p.n_steps + key)] = (uint32_t)row;
+        if (tail) p.range[2 * ((size_t)fam * p.n_steps + key) + 1] = (uint32_t)(row + 1);
+      }
+      // A tail lane stores its segment's sum (seg_scan): into the tile's carry
+      // slot if the segment continues from the previous tile, else into the
+      // (spec, family, step) partial.
+      seg_factors(key, fac);
+      // the scan input is m t for a live record of multiplicity m (1 without
+      // a multiplicity array) and 0 otherwise: one product per spec instead
+      // of a select.  A lane that is not live either repeats lane 0's record
+      // (a tail lane past nvalid, whose t is finite whenever lane 0's is) or
+      // is flagged bad data; both sit at or after the wave's last live lane or
+      // carry a flagged record, so the scan of every live segment is unchanged.
+      tfac = MULT ? (live ? fc.mult : 0.0f) : 0.0f;
+      // (spec-minor layout: a tail lane's sums for all specs are one
+      // contiguous run, so its stores fill whole cache lines)
+      if (p.partial && is_tail) {
+        if (to_carry)
+          dst = p.carry + (size_t)tile_id * (size_t)p.n_specs;
+        else
+          dst = p.partial + ((size_t)fam * (size_t)p.n_steps + key) * (size_t)p.n_specs;
+      }
     }
 
     if constexpr (PipeOK<H>::value && !GRID) {
@@ -1607,8 +1667,8 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
             if constexpr (a.eta) eta_prev = 1.0f + __expf(-H::tail_reduce(zp, lds));
             if constexpr (a.tail) {
               if (s > 0)
-                spec_tail<MULT>(p, s_lo + s - 1, tr_prev, eta_prev, fmaxf(tr_prev * eta_prev, t0_prev), valid, live,
-                                row, tfac, fac, dst);
+                spec_tail<MULT, UNIQ>(p, s_lo + s - 1, tr_prev, eta_prev, fmaxf(tr_prev * eta_prev, t0_prev), valid, live,
+                                      row, tfac, fac, dst, u_dst);
             }
             if constexpr (NEXT && a.roof) on = small ? roofline<true>(rc, sn) : roofline<false>(rc, sn);
             if constexpr (NEXT && a.feat != 0u) {
@@ -1644,8 +1704,8 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
         H::tail_pairs(st, zl, 0, 4);
         H::tail_pairs(st, zl, 4, 8);
         const float eta = 1.0f + __expf(-H::tail_reduce(zl, lds));
-        spec_tail<MULT>(p, s_lo + S - 1, tr_prev, eta, fmaxf(tr_prev * eta, t0_prev), valid, live, row, tfac, fac,
-                        dst);
+        spec_tail<MULT, UNIQ>(p, s_lo + S - 1, tr_prev, eta, fmaxf(tr_prev * eta, t0_prev), valid, live, row, tfac,
+                              fac, dst, u_dst);
         continue;
       }
     }
@@ -1679,10 +1739,10 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
       const float t = fmaxf(o.t_roof * eta, sc.t0);
       // (without a grid the source is a per-family constant, written by
       // k_fill_source instead, so the plain kernels keep their registers)
-      if constexpr (GRID) {
+      if constexpr (GRID && !UNIQ) {
         if (valid && p.o_src) p.o_src[(size_t)s * (size_t)p.fam_off[KS_NFAM] + (size_t)row] = routed ? 2 : (bnd ? 1 : 0);
       }
-      spec_tail<MULT>(p, s, o.t_roof, eta, t, valid, live, row, tfac, fac, dst);
+      spec_tail<MULT, UNIQ>(p, s, o.t_roof, eta, t, valid, live, row, tfac, fac, dst, u_dst);
     }
   }
 }
@@ -2270,101 +2330,6 @@ __global__ void k_fill_source(uint8_t *src, EvalParams p) {
   }
 }
 
-// ------------------------------------------------------------ step finish
-// per (spec, step): t_body, t_comm (Eq. 3, two all-reduces per layer),
-// t_gpu and t_step (Eq. 4).  The partial sums are spec-minor and the
-// outputs step-minor, so a workgroup takes a tile of kFinSteps steps x
-// kFinSpecs specs (kFinSpecs a power of two, at least the spec count or
-// 16): it reads with the spec fastest, passes the three results through
-// LDS, and writes with the step fastest.
-constexpr int kFinThreads = 256;
-
-__global__ __launch_bounds__(kFinThreads) void k_finish(FinishParams p, int spec_bits) {
-  __shared__ double res[3][kFinThreads];
-  const int tps = 1 << spec_bits;                 // specs per tile
-  const int tst = kFinThreads >> spec_bits;        // steps per tile
-  const int64_t n_st = (p.n_steps + tst - 1) / tst;
-  const int64_t n_sp = (p.n_specs + tps - 1) / tps;
-  const int tid = threadIdx.x;
-  for (int64_t tile = blockIdx.x; tile < n_st * n_sp; tile += gridDim.x) {
-    const int64_t j0 = (tile % n_st) * tst;
-    const int s0 = (int)(tile / n_st) * tps;
-    // phase 1: thread (step jj, spec ss), spec fastest
-    {
-      const int ss = tid & (tps - 1), jj = tid >> spec_bits;
-      const int s = s0 + ss;
-      const int64_t j = j0 + jj;
-      if (s < p.n_specs && j < p.n_steps) {
-        const size_t S = (size_t)p.n_specs;
-        // every family's range, then its partial and first carry, are
-        // loaded before any is summed (independent loads in flight together
-        // instead of a chain of ten); the sum keeps family order: partial,
-        // then the carries of its later tiles
-        uint32_t r0[KS_NFAM], r1[KS_NFAM];
-#pragma unroll
-        for (int f = 0; f < KS_NFAM; ++f) {
-          r0[f] = p.range[2 * (f * p.n_steps + j)];
-          r1[f] = p.range[2 * (f * p.n_steps + j) + 1];
-        }
-        bool any[KS_NFAM];
-        int t_first[KS_NFAM], t_last[KS_NFAM];
-        double part[KS_NFAM], car1[KS_NFAM];
-#pragma unroll
-        for (int f = 0; f < KS_NFAM; ++f) {
-          // clamped to the family's rows: a range left half-written by
-          // unsorted input (reported by ks_validate) still indexes only this
-          // family's tiles
-          const int64_t base = p.fam_off[f], top = p.fam_off[f + 1];
-          int64_t a = r0[f], b = r1[f];
-          a = a < base ? base : (a > top ? top : a);
-          b = b < base ? base : (b > top ? top : b);
-          any[f] = a < b;
-          t_first[f] = any[f] ? p.tile_off[f] + (int)((a - base) / kTileRows) : 0;
-          t_last[f] = any[f] ? p.tile_off[f] + (int)((b - 1 - base) / kTileRows) : 0;
-          part[f] = any[f] ? p.partial[((size_t)f * (size_t)p.n_steps + (size_t)j) * S + s] : 0.0;
-          car1[f] = t_last[f] > t_first[f] ? p.carry[(size_t)(t_first[f] + 1) * S + s] : 0.0;
-        }
-        double body = 0.0;
-#pragma unroll
-        for (int f = 0; f < KS_NFAM; ++f) {
-          if (!any[f]) continue;
-          body += part[f];
-          if (t_last[f] > t_first[f]) body += car1[f];
-          for (int t = t_first[f] + 2; t <= t_last[f]; ++t) body += p.carry[(size_t)t * S + s];
-        }
-        const ks_spec sp = p.specs[s];
-        const double P = (double)p.tp[j];
-        const double Sb = (double)p.agg[j] * (double)p.hidden[j] * (double)p.elem_bytes;
-        double t_ar = 0.0;
-        if (P > 1.0)
-          t_ar = sp.ar_alpha0 + sp.ar_alpha_log2p * log2(P) + 2.0 * (P - 1.0) / P * Sb / sp.ar_beta;
-        const double comm = 2.0 * (double)p.layers[j] * t_ar;
-        const double gpu = p.host.body_scale * body + comm;
-        const double step = fmax(gpu + (double)p.n_launch[j] * p.host.c_disp, p.host.ell) +
-                            fmax(0.0, p.host.c_ovl - gpu) + p.host.c_tail;
-        res[0][ss * tst + jj] = body;
-        res[1][ss * tst + jj] = gpu;
-        res[2][ss * tst + jj] = step;
-      }
-    }
-    __syncthreads();
-    // phase 2: thread (spec ss, step jj), step fastest
-    {
-      const int jj = tid % tst, ss = tid / tst;
-      const int s = s0 + ss;
-      const int64_t j = j0 + jj;
-      if (s < p.n_specs && j < p.n_steps) {
-        const size_t o = (size_t)s * (size_t)p.n_steps + (size_t)j;
-        p.t_body[o] = res[0][ss * tst + jj];
-        p.t_gpu[o] = res[1][ss * tst + jj];
-        p.t_step[o] = res[2][ss * tst + jj];
-        if (p.own && p.own[j] == (uint32_t)s) p.lat[j] = res[2][ss * tst + jj];
-      }
-    }
-    __syncthreads();
-  }
-}
-
 // ------------------------------------------------------------ validation
 __global__ void k_validate(ValidateParams p) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -2594,7 +2559,7 @@ static hipError_t launch_kind(const EvalParams &p, hipStream_t s) {
   return mult ? launch_grid<KIND, kVarMult>(p, s) : launch_grid<KIND, 0>(p, s);
 }
 
-hipError_t launch_eval(int kind, const EvalParams &p, hipStream_t s) {
+static hipError_t launch_direct(int kind, const EvalParams &p, hipStream_t s) {
   if (p.wgt_off[KS_NFAM] == 0) return hipSuccess;
   switch (kind) {
     case kEtaOne: return launch_eta_one(p, s);
@@ -2613,20 +2578,69 @@ hipError_t launch_eval(int kind, const EvalParams &p, hipStream_t s) {
   }
 }
 
+template <int KIND, int VAR>
+static hipError_t launch_uniq_grid(const EvalParams &p, hipStream_t s) {
+  int cap = 0;
+  const hipError_t e = resident_wgs<KIND, VAR>(&cap);
+  if (e != hipSuccess) return e;
+  // (how many tiles there are is known on the device only: k_eval splits the
+  // spec loop by itself, and workgroups without work leave at once)
+  int64_t most = 0;
+  for (int f = 0; f < KS_NFAM; ++f)
+    if ((p.uniq_mask >> f) & 1u) most += (p.u_cap[f] + kWgRows - 1) / kWgRows;
+  most *= p.n_specs;
+  hipLaunchKernelGGL((k_eval<KIND, VAR>), dim3((int)(most < cap ? most : cap)), dim3(kWgThreads), 0, s, p);
+  return hipGetLastError();
+}
+
+template <int KIND>
+static hipError_t launch_uniq(const EvalParams &p, hipStream_t s) {
+  return p.grid_mask ? launch_uniq_grid<KIND, kVarUniq | kVarGrid>(p, s) : launch_uniq_grid<KIND, kVarUniq>(p, s);
+}
+
+static hipError_t launch_uniq_kind(int kind, const EvalParams &p, hipStream_t s) {
+  switch (kind) {
+    case kF32_16_64: return launch_uniq<kF32_16_64>(p, s);
+    case kF32_16_128: return launch_uniq<kF32_16_128>(p, s);
+    case kF32_32_64: return launch_uniq<kF32_32_64>(p, s);
+    case kF32_32_128: return launch_uniq<kF32_32_128>(p, s);
+    case kBF16_16_64: return launch_uniq<kBF16_16_64>(p, s);
+    case kBF16_16_128: return launch_uniq<kBF16_16_128>(p, s);
+    case kBF16_16_256: return launch_uniq<kBF16_16_256>(p, s);
+    case kBF16_32_64: return launch_uniq<kBF16_32_64>(p, s);
+    case kBF16_32_128: return launch_uniq<kBF16_32_128>(p, s);
+    case kBF16_32_256: return launch_uniq<kBF16_32_256>(p, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// p restricted to the families of `mask` (their work; the tile numbers of the
+// carries stay those of the whole call)
+static EvalParams families_of(const EvalParams &p, uint32_t mask) {
+  EvalParams q = p;
+  q.wgt_off[0] = 0;
+  for (int f = 0; f < KS_NFAM; ++f)
+    q.wgt_off[f + 1] = q.wgt_off[f] + ((mask >> f) & 1u ? p.wgt_off[f + 1] - p.wgt_off[f] : 0);
+  return q;
+}
+
+hipError_t launch_eval(int kind, const EvalParams &p, hipStream_t s) {
+  if (!p.uniq) return launch_direct(kind, p, s);
+  hipError_t e = launch_unique(*p.uniq, s);
+  if (e == hipSuccess) e = launch_uniq_kind(kind, p, s);
+  // the families it leaves out, then (each workgroup returning at once unless
+  // the different records did not fit) the others, every record
+  EvalParams q = families_of(p, ~p.uniq_mask);
+  q.u_over = nullptr;
+  if (e == hipSuccess) e = launch_direct(kind, q, s);
+  if (e == hipSuccess && p.uniq->may_overflow) e = launch_direct(kind, families_of(p, p.uniq_mask), s);
+  return e;
+}
+
 hipError_t launch_fill_source(const EvalParams &p, hipStream_t s) {
   const int64_t total = (int64_t)p.n_specs * p.fam_off[KS_NFAM];
   if (!p.o_src || total == 0) return hipSuccess;
   hipLaunchKernelGGL(k_fill_source, dim3(grid_for(total, 256, 8192)), dim3(256), 0, s, p.o_src, p);
-  return hipGetLastError();
-}
-
-hipError_t launch_finish(const FinishParams &p, hipStream_t s) {
-  if (p.n_steps == 0) return hipSuccess;
-  int bits = 0;   // specs per tile: the spec count rounded up to a power of two, at most 16
-  while (bits < 4 && (1 << bits) < p.n_specs) ++bits;
-  const int64_t tiles = ((p.n_steps + (kFinThreads >> bits) - 1) / (kFinThreads >> bits)) *
-                        (((int64_t)p.n_specs + (1 << bits) - 1) >> bits);
-  hipLaunchKernelGGL(k_finish, dim3(grid_for(tiles, 1, 8192)), dim3(kFinThreads), 0, s, p, bits);
   return hipGetLastError();
 }
 

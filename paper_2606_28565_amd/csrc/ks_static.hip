@@ -55,8 +55,11 @@ extern "C" ks_status ks_eval_steps_static(const ks_desc *desc, const ks_steps *s
                                           hipStream_t stream) {
   // size check before any runtime call: bad arguments get the evaluation's
   // own message (its checks run before its first launch)
-  const size_t need = ks_workspace_bytes(desc, n_specs);
-  if (need == 0) return ks_eval_steps(desc, steps, specs, n_specs, heads, host, out, kout, nullptr, 0, stream);
+  if (ks_workspace_bytes(desc, n_specs) == 0)
+    return ks_eval_steps(desc, steps, specs, n_specs, heads, host, out, kout, nullptr, 0, stream);
+  // what the evaluation cannot do without (with less than ks_workspace_bytes()
+  // it evaluates every record instead of the different ones)
+  const size_t need = ks::eval_workspace_bytes(desc->fam_off, desc->n_steps, n_specs);
   if (need > (size_t)KS_STATIC_SCRATCH_BYTES)
     return ks::set_error(KS_ERANGE,
                          "this call needs %zu bytes of workspace, above the %d-byte static scratch; "

@@ -1,0 +1,178 @@
+"""Step sums over the different records of a call (GPU): calls with enough
+head work evaluate equal records once and weight them.  The reference is the
+same call with per-pair outputs, which evaluates every record: its t_kernel
+summed in float64 per step.  Both paths form the same fp32 t for a record, and
+the weights (counts times multiplicities below 2^24) are exact in fp32, so only
+the order of the float64 sums differs: with at most 4096 non-negative terms a
+step, 4096 2^-53 < 1e-12 relative."""
+import numpy as np
+import pytest
+
+from paper_2606_28565_amd import abi
+from tests import gpu_helpers as g
+from tests.helpers import make_desc, steprec
+from workload import gen
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-12
+
+
+def _wl(rows, reqs, heads, n_specs, mult=None, expert_rows=()):
+    d = make_desc(rows, reqs, expert_rows)
+    if mult is not None:
+        d.mult = np.asarray(mult(d.n_rows), np.uint32)
+    return gen.Workload("unique", d, steprec(len(reqs), layers=3, hidden=4096, tp=2, n_launch=1),
+                        gen.specs_grid(n_specs, 77), heads, gen.HostConsts())
+
+
+def _check(wl, grid=None, tol=TOL):
+    pairs = g.eval_steps(wl, counts=False, grid=grid)
+    sums = g.eval_steps(wl, per_pair=False, grid=grid)
+    d = wl.desc
+    w = np.ones(d.n_rows) if getattr(d, "mult", None) is None else d.mult.astype(np.float64)
+    for s in range(wl.n_specs):
+        body = np.bincount(d.step, weights=pairs["t_kernel"][s].astype(np.float64) * w, minlength=d.n_steps)
+        np.testing.assert_allclose(sums["t_body"][s], body, rtol=tol)
+    for k in ("t_gpu", "t_step"):   # the other path's sums are fp32 within 64-record tiles
+        np.testing.assert_allclose(sums[k], pairs[k], rtol=1e-6)
+
+
+def _reqs(rng, n):
+    return [[(int(rng.integers(1, 300)), int(rng.integers(0, 4000))) for _ in range(int(rng.integers(1, 4)))]
+            for _ in range(n)]
+
+
+def _family(rng, f, step, kernels, layers):
+    """`layers` repeats of `kernels` different records of family f."""
+    m = [int(x) for x in rng.integers(1, 3000, kernels)]
+    n = [int(x) for x in rng.integers(1, 200, kernels)]
+    return [(f, step, m[i], n[i], 128, 4, 0) for _ in range(layers) for i in range(kernels)]
+
+
+@pytest.mark.parametrize("kernels", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("layers", [1, 7, 80])
+def test_layers_repeat(kernels, layers):
+    """Periods 1 to 4 and none (5), pieces that start anywhere in a chunk and
+    cross its end, odd family offsets, steps without a family.  More than eight
+    records per step without a period do not fit and are all evaluated, their
+    sums fp32 within 64-record tiles: at most 6 levels of adds, 6 2^-24."""
+    rng = np.random.Generator(np.random.PCG64(kernels * 100 + layers))
+    n_steps = max(37, 9000 // (kernels * layers * 3))
+    fams = (gen.GEMM, gen.ATTN_DECODE, gen.RMSNORM)
+    rows = []
+    for j in range(n_steps):
+        for f in fams:
+            if rng.random() < 0.9:
+                rows += _family(rng, f, j, kernels, layers if rng.random() < 0.8 else layers + 1)
+    wl = _wl(rows, _reqs(rng, n_steps), gen.make_heads(16, 128, "bf16"), 160)
+    _check(wl, tol=6 * 2.0 ** -24 if kernels == 5 and layers > 1 else TOL)
+
+
+@pytest.mark.parametrize("run", [1, 1023, 1024, 1025, 3000])
+def test_one_long_step_and_chunk_edges(run):
+    """A step of `run` equal records among steps of one: pieces that end at,
+    before and after a chunk's edge, and steps that span several chunks."""
+    rng = np.random.Generator(np.random.PCG64(run))
+    rows = [(gen.ROPE, 0, 17, 8, 128, 0, 0)]
+    rows += [(gen.ROPE, 1, 33, 8, 128, 0, 0)] * run
+    rows += [(gen.ROPE, 2 + i, int(rng.integers(1, 64)), 8, 128, 0, 0) for i in range(2100)]
+    wl = _wl(rows, _reqs(rng, 2102), gen.make_heads(32, 64, "f32"), 64)
+    _check(wl)
+
+
+@pytest.mark.parametrize("precision,in_dim,hidden,n_specs", [("f32", 16, 64, 64), ("bf16", 32, 256, 64),
+                                                             ("bf16", 16, 64, 400)])
+def test_multiplicities_and_shared_slots(precision, in_dim, hidden, n_specs):
+    """Multiplicities (equal records with different ones stay apart), and token
+    counts a table's size apart, which meet in one slot."""
+    rng = np.random.Generator(np.random.PCG64(5))
+    rows = []
+    for j in range(600):
+        for m in (3, 3 + (1 << 15), 3 + (1 << 18), int(rng.integers(1, 9))):
+            rows += [(gen.LM_HEAD, j, m, 1000, 4096, 0, 0), (gen.GEMM, j, m, 96, 4096, 0, 0),
+                     (gen.GEMM, j, m, 97, 4096, 0, 0)]
+    wl = _wl(rows, _reqs(rng, 600), gen.make_heads(in_dim, hidden, precision), n_specs,
+             mult=lambda n: rng.integers(0, 3, n) * 40)
+    _check(wl)
+
+
+def test_records_that_do_not_repeat_fall_back():
+    """Many records per step, none equal: more entries than there is room for,
+    so every record is evaluated; beside a family that repeats."""
+    rng = np.random.Generator(np.random.PCG64(6))
+    rows = []
+    for j in range(24):
+        rows += [(gen.GEMM, j, 1 + i + 200 * j, 512, 256, 0, 0) for i in range(200)]
+        rows += [(gen.RMSNORM, j, 5 + j, 4096, 0, 0, 0)] * 64
+    wl = _wl(rows, _reqs(rng, 24), gen.make_heads(16, 128, "bf16"), 160)
+    pairs, sums = g.eval_steps(wl, counts=False), g.eval_steps(wl, per_pair=False)
+    for k in ("t_body", "t_gpu", "t_step"):   # both evaluate every record, alike
+        np.testing.assert_array_equal(sums[k], pairs[k])
+
+
+@pytest.mark.parametrize("grids", [False, True])
+def test_grouped_gemms_and_grids(grids):
+    """Grouped GEMMs keep a record per layer (summed in fp32 within 64-record
+    tiles: 6 2^-24) beside families that repeat; with and without measured
+    grids."""
+    rng = np.random.Generator(np.random.PCG64(7))
+    rows, experts = [], []
+    for j in range(40):
+        for layer in range(16):
+            rows += [(gen.GROUPED_GEMM, j, 0, 28672, 4096, 8, len(experts)),
+                     (gen.GROUPED_GEMM, j, 0, 4096, 14336, 8, len(experts))]
+            experts += [int(x) for x in rng.integers(0, 300, 8)]
+        rows += _family(rng, gen.GEMM, j, 3, 16) + _family(rng, gen.SILU_MUL, j, 1, 16)
+    wl = _wl(rows, _reqs(rng, 40), gen.make_heads(16, 128, "bf16"), 200, expert_rows=experts)
+    _check(wl, grid=gen.make_grid(gen.GRID_ALL) if grids else None, tol=6 * 2.0 ** -24)
+
+
+def test_bad_steps_are_skipped_and_reported():
+    """Records whose step is out of range are left out and flagged."""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(8))
+    rows = [(gen.ROPE, j, 1 + j % 50, 8, 128, 0, 0) for j in range(4000)]
+    good = _wl(rows, _reqs(rng, 4000), gen.make_heads(16, 128, "bf16"), 200)
+    bad = _wl(rows + [(gen.ROPE, 4000 + i, 3, 8, 128, 0, 0) for i in range(1500)], [[(1, 1)]] * 4000,
+              gen.make_heads(16, 128, "bf16"), 200)
+    bad.desc.req_off, bad.desc.req_q, bad.desc.req_h = good.desc.req_off, good.desc.req_q, good.desc.req_h
+    ref = g.eval_steps(good, per_pair=False)
+    di = abi.DeviceInputs(bad)
+    so_t, so = abi.step_outputs(bad.desc.n_steps, di.n_specs)
+    abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, di.n_specs, di.heads, di.host, so, None, di.ws_ptr,
+                      di.ws_bytes, abi.current_stream())
+    torch.cuda.synchronize()
+    st = abi.ks_device_status(di.ws_ptr, di.ws_bytes, abi.current_stream(), check=False)
+    assert st == abi.KS_EINVAL
+    for k in ("t_body", "t_gpu", "t_step"):
+        np.testing.assert_allclose(so_t[k].cpu().numpy(), ref[k], rtol=TOL)
+
+
+@pytest.mark.parametrize("n_specs", [1, 2, 3, 4, 5, 16, 33])
+def test_workspace_without_room_evaluates_every_record(n_specs):
+    """The step sums' kernels by spec count, and the same call in a workspace
+    with no room for the different records (as large as the part both forms
+    use): equal within the fp32 tile sums of the latter."""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(9))
+    rows = []
+    n_steps = 6000 // n_specs + 50
+    for j in range(n_steps):
+        rows += _family(rng, gen.GEMM, j, 4, 20) + [(gen.ATTN_DECODE, j, 0, 32, 128, 8, 0)] * 20
+        rows += [(gen.LM_HEAD, j, 1 + j % 64, 32000, 4096, 0, 0)]
+    wl = _wl(rows, _reqs(rng, n_steps), gen.make_heads(32, 128, "f32"), n_specs)
+    _check(wl)
+    di = abi.DeviceInputs(wl)
+    outs = []
+    tiles = sum(-(-int(k) // 64) for k in np.diff(wl.desc.fam_off))
+    small = 256 + 256 * (-(-64 * n_specs // 256)) + 256 * 4 + 32 * n_steps + 80 * n_steps \
+        + 80 * n_specs * n_steps + 8 * n_specs * tiles + 256
+    assert small < di.ws_bytes
+    for wsb in (di.ws_bytes, small):
+        so_t, so = abi.step_outputs(n_steps, n_specs)
+        abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, n_specs, di.heads, di.host, so, None, di.ws_ptr, wsb,
+                          abi.current_stream())
+        torch.cuda.synchronize()
+        outs.append({k: v.cpu().numpy() for k, v in so_t.items()})
+    for k in outs[0]:
+        np.testing.assert_allclose(outs[0][k], outs[1][k], rtol=1e-6)
