@@ -1074,16 +1074,31 @@ struct HeadBF16 {
 };
 
 // ------------------------------------------------------------ fp32 MFMA head
-// Same orientation with v_mfma_f32_32x32x2_f32 (K = 2 per instruction):
-//   A[i][k]: lane l holds row l % 32, k = g;  B[k][j]: col l % 32, k = g;
-//   C as for the bf16 instruction.
+// fp32 operands on the bf16 matrix instruction, which does 16 times the work of
+// the fp32 one per cycle: every operand is split exactly into three bfloat16
+// pieces of 8 bits (x = x0 + x1 + x2, each the rest rounded to nearest), and of
+// the nine products of pieces the six down to 2^-17 of the whole are formed,
+// each exact in fp32.  What is left out is below 2^-26 of a product, a quarter
+// of the rounding of one fp32 product.  The leading products and the others
+// are summed apart (fp32, in the instruction) and added at the end, so that
+// the leading sum is rounded once per 16 terms rather than once per 2: eta's
+// root mean square error against 64 bits went from 4.8e-8 to 4.7e-8 (16-128)
+// and from 4.6e-8 to 4.2e-8 (32-128), its largest from 2.1e-7 to 1.2e-7.
+// 480 instructions of 32 cycles per wave and spec (32-128) instead of 640 of
+// 64: 704k pairs 303 -> 167 us, of which the matrix core is busy 60%, as in the
+// bf16 heads (running the split of one block under the products of the next,
+// by the compiler's group barriers or by hand, gave 167 to 177 us: the clock
+// under this load is 1.8 GHz).  Orientation, lane layout and hidden-unit order
+// are the bf16 head's.
 template <int IN, int HID>
 struct HeadF32 {
   static constexpr bool kRaw = false;
+  using B = HeadBF16<IN, HID>;
   static constexpr int MB = HID / 32;
-  static constexpr int C1 = IN / 2;
-  static constexpr int W1_DW = MB * C1 * 64;
-  static constexpr int W2_DW = MB * MB * 64 * 16;
+  static constexpr int KC1 = IN / 16, KC2 = HID / 16;
+  static constexpr int kFrag = 3 * 64 * 4;             // dwords of one fragment's three pieces
+  static constexpr int W1_DW = MB * KC1 * kFrag;
+  static constexpr int W2_DW = MB * KC2 * kFrag;
   static constexpr int B2_DW = MB * 2 * 16;
   static constexpr int W3_DW = MB * 2 * 16;
   static constexpr int OFF_W2 = W1_DW;
@@ -1093,8 +1108,15 @@ struct HeadF32 {
   static constexpr int LDS_DW = OFF_B3 + 4;
   static constexpr bool kMlp = true;
 
-  __device__ static __forceinline__ int out_of(int mb, int g, int r) {
-    return mb * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+  // a pair of values as three packed pairs of pieces
+  __device__ static __forceinline__ void split(float a, float b, uint32_t &p0, uint32_t &p1, uint32_t &p2) {
+    p0 = pack_bf16(a, b);
+    a -= __builtin_bit_cast(float, p0 << 16);
+    b -= __builtin_bit_cast(float, p0 & 0xFFFF0000u);
+    p1 = pack_bf16(a, b);
+    a -= __builtin_bit_cast(float, p1 << 16);
+    b -= __builtin_bit_cast(float, p1 & 0xFFFF0000u);
+    p2 = pack_bf16(a, b);
   }
 
   __device__ static void stage(uint32_t *lds, int fam, const EvalParams &p) {
@@ -1103,76 +1125,103 @@ struct HeadF32 {
     const float *b2 = (const float *)p.b2 + (size_t)fam * HID;
     const float *w3 = (const float *)p.w3 + (size_t)fam * HID;
     float *f = (float *)lds;
-    for (int d = threadIdx.x; d < W1_DW; d += kWgThreads) {
-      const int lane = d & 63, c = (d >> 6) % C1, mb = (d >> 6) / C1;
-      f[d] = w1[(mb * 32 + (lane & 31)) * IN + 2 * c + (lane >> 5)];
+    for (int d = threadIdx.x; d < MB * KC1 * 256; d += kWgThreads) {
+      const int q = d & 3, lane = (d >> 2) & 63, frag = d >> 8;
+      const int kc = frag % KC1, mb = frag / KC1;
+      const float *w = w1 + (mb * 32 + (lane & 31)) * IN + kc * 16 + (lane >> 5) * 8 + 2 * q;
+      uint32_t *o = lds + frag * kFrag + (d & 255);
+      split(w[0], w[1], o[0], o[256], o[512]);
     }
-    // [mb2][mb][lane][r]: W2[out = mb2 32 + l % 32][in = out_of(mb, g, r)]
-    for (int d = threadIdx.x; d < W2_DW; d += kWgThreads) {
-      const int r = d & 15, lane = (d >> 4) & 63, blk = d >> 10;
-      const int mb = blk % MB, mb2 = blk / MB;
-      f[OFF_W2 + d] = w2[(mb2 * 32 + (lane & 31)) * HID + out_of(mb, lane >> 5, r)];
+    for (int d = threadIdx.x; d < MB * KC2 * 256; d += kWgThreads) {
+      const int q = d & 3, lane = (d >> 2) & 63, frag = d >> 8;
+      const int kc = frag % KC2, mb = frag / KC2;
+      // (hid_of of an even slot and the next are consecutive units)
+      const float *w = w2 + (mb * 32 + (lane & 31)) * HID + B::hid_of(kc, (lane >> 5) * 8 + 2 * q);
+      uint32_t *o = lds + OFF_W2 + frag * kFrag + (d & 255);
+      split(w[0], w[1], o[0], o[256], o[512]);
     }
     for (int d = threadIdx.x; d < B2_DW; d += kWgThreads) {
       const int r = d & 15, g = (d >> 4) & 1, mb = d >> 5;
-      f[OFF_B2 + d] = b2[out_of(mb, g, r)];
-      f[OFF_W3 + d] = w3[out_of(mb, g, r)];
+      f[OFF_B2 + d] = b2[B::out_of(mb, g, r)];
+      f[OFF_W3 + d] = w3[B::out_of(mb, g, r)];
     }
     if (threadIdx.x == 0) f[OFF_B3] = ((const float *)p.b3)[fam];
+  }
+
+  // hi += a0 b0; lo += the five products below it; for the two column blocks
+  // in turn, so that no instruction waits for the one before it
+  __device__ static __forceinline__ void product(const uint32_t *frag, int lane, const u32x4 (&b)[3], const u32x4 (&d)[3],
+                                                 f32x16 (&hi)[2], f32x16 (&lo)[2]) {
+    const u32x4 a0 = *(const u32x4 *)(frag + lane * 4), a1 = *(const u32x4 *)(frag + 256 + lane * 4),
+                a2 = *(const u32x4 *)(frag + 512 + lane * 4);
+    lo[0] = B::mfma(a2, b[0], lo[0]);
+    lo[1] = B::mfma(a2, d[0], lo[1]);
+    hi[0] = B::mfma(a0, b[0], hi[0]);
+    hi[1] = B::mfma(a0, d[0], hi[1]);
+    lo[0] = B::mfma(a1, b[1], lo[0]);
+    lo[1] = B::mfma(a1, d[1], lo[1]);
+    lo[0] = B::mfma(a0, b[2], lo[0]);
+    lo[1] = B::mfma(a0, d[2], lo[1]);
+    lo[0] = B::mfma(a1, b[0], lo[0]);
+    lo[1] = B::mfma(a1, d[0], lo[1]);
+    lo[0] = B::mfma(a0, b[1], lo[0]);
+    lo[1] = B::mfma(a0, d[1], lo[1]);
   }
 
   __device__ static __forceinline__ float mlp(const float (&x)[IN], const uint32_t *lds) {
     const int lane = threadIdx.x & 63, g = lane >> 5;
     const float *f = (const float *)lds;
-    float XB[2][C1];
+    u32x4 X[2][KC1][3];
+    {
+      uint32_t P[3][IN / 2];
 #pragma unroll
-    for (int c = 0; c < C1; ++c) {
-      uint32_t lo = __builtin_bit_cast(uint32_t, x[2 * c]);
-      uint32_t hi = __builtin_bit_cast(uint32_t, x[2 * c + 1]);
-      swap32(lo, hi);
-      XB[0][c] = __builtin_bit_cast(float, lo);
-      XB[1][c] = __builtin_bit_cast(float, hi);
+      for (int c = 0; c < IN / 2; ++c) split(x[2 * c], x[2 * c + 1], P[0][c], P[1][c], P[2][c]);
+#pragma unroll
+      for (int kc = 0; kc < KC1; ++kc)
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            uint32_t lo = P[i][8 * kc + q], hi = P[i][8 * kc + 4 + q];
+            swap32(lo, hi);
+            X[0][kc][i][q] = lo;
+            X[1][kc][i][q] = hi;
+          }
     }
-    f32x16 H1[2][MB];
+    u32x4 H[2][KC2][3];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-      f32x16 c0 = {}, c1 = {};
+      f32x16 hi[2] = {f32x16{}, f32x16{}}, lo[2] = {f32x16{}, f32x16{}};
 #pragma unroll
-      for (int c = 0; c < C1; ++c) {
-        const float a = f[(mb * C1 + c) * 64 + lane];
-        c0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, XB[0][c], c0, 0, 0, 0);
-        c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, XB[1][c], c1, 0, 0, 0);
-      }
+      for (int kc = 0; kc < KC1; ++kc) product(lds + (mb * KC1 + kc) * kFrag, lane, X[0][kc], X[1][kc], hi, lo);
+      // registers 8 h .. 8 h + 7 of the block are K chunk 2 mb + h of layer 2
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        c0[r] = fmaxf(c0[r], 0.0f);
-        c1[r] = fmaxf(c1[r], 0.0f);
-      }
-      H1[0][mb] = c0;
-      H1[1][mb] = c1;
-    }
-    float z0 = 0.0f, z1 = 0.0f;
-#pragma unroll 1
-    for (int mb2 = 0; mb2 < MB; ++mb2) {
-      const f32x16 bias = *(const f32x16 *)(f + OFF_B2 + (mb2 * 2 + g) * 16);
-      f32x16 c0 = bias, c1 = bias;
+      for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const float *a = f + OFF_W2 + ((mb2 * MB + mb) * 64 + lane) * 16;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          c0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[r], H1[0][mb][r], c0, 0, 0, 0);
-          c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[r], H1[1][mb][r], c1, 0, 0, 0);
+        for (int q = 0; q < 8; ++q) {
+          uint32_t p0, p1, p2;
+          split(relu_f(hi[c][2 * q] + lo[c][2 * q]), relu_f(hi[c][2 * q + 1] + lo[c][2 * q + 1]), p0, p1, p2);
+          H[c][2 * mb + (q >> 2)][0][q & 3] = p0;
+          H[c][2 * mb + (q >> 2)][1][q & 3] = p1;
+          H[c][2 * mb + (q >> 2)][2][q & 3] = p2;
         }
-      }
-      const float *w3 = f + OFF_W3 + (mb2 * 2 + g) * 16;
+    }
+    float z[2] = {0.0f, 0.0f};
+#pragma unroll 1
+    for (int mb = 0; mb < MB; ++mb) {
+      const f32x16 bias = *(const f32x16 *)(f + OFF_B2 + (mb * 2 + g) * 16);
+      f32x16 hi[2] = {bias, bias}, lo[2] = {f32x16{}, f32x16{}};
+#pragma unroll
+      for (int kc = 0; kc < KC2; ++kc)
+        product(lds + OFF_W2 + (mb * KC2 + kc) * kFrag, lane, H[0][kc], H[1][kc], hi, lo);
+      const float *w3 = f + OFF_W3 + (mb * 2 + g) * 16;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        z0 = fmaf(w3[r], fmaxf(c0[r], 0.0f), z0);
-        z1 = fmaf(w3[r], fmaxf(c1[r], 0.0f), z1);
+        z[0] = fmaf(w3[r], relu_f(hi[0][r] + lo[0][r]), z[0]);
+        z[1] = fmaf(w3[r], relu_f(hi[1][r] + lo[1][r]), z[1]);
       }
     }
-    uint32_t a0 = __builtin_bit_cast(uint32_t, z0), a1 = __builtin_bit_cast(uint32_t, z1);
+    uint32_t a0 = __builtin_bit_cast(uint32_t, z[0]), a1 = __builtin_bit_cast(uint32_t, z[1]);
     swap32(a0, a1);
     return __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1) + f[OFF_B3];
   }
@@ -1262,6 +1311,8 @@ __device__ __forceinline__ float seg_scan(float v, const float (&f)[6]) {
 // shared.  Workgroups stride over workgroup tiles and restage only when the
 // family changes (records are family-major).
 template <int KIND> struct MinWg { static constexpr int value = 1; };
+template <> struct MinWg<kF32_16_64> { static constexpr int value = 2; };
+template <> struct MinWg<kF32_32_64> { static constexpr int value = 2; };
 template <> struct MinWg<kBF16_16_64> { static constexpr int value = 2; };
 template <> struct MinWg<kBF16_16_128> { static constexpr int value = 2; };
 template <> struct MinWg<kBF16_32_64> { static constexpr int value = 2; };

@@ -294,6 +294,23 @@ def test_bf16_weights_at_unaligned_addresses(in_dim, hidden):
         np.testing.assert_array_equal(unaligned[k], aligned[k], err_msg=k)
 
 
+@pytest.mark.parametrize("in_dim,hidden", [(16, 64), (32, 64), (16, 128), (32, 128)])
+@pytest.mark.parametrize("shift", [-60, -13, 11, 50])
+def test_f32_heads_scale_by_powers_of_two(in_dim, hidden, shift):
+    """The fp32 heads split their operands into bfloat16 pieces.  The split is
+    exact and follows the exponent, so W1 times 2^shift and W2 times 2^-shift
+    (relu is homogeneous) give bit-identical outputs, as fp32 arithmetic does."""
+    import dataclasses
+    heads = gen.make_heads(in_dim, hidden, "f32")
+    scaled = {k: v.copy() for k, v in heads.storage.items()}
+    scaled["w1"] = scaled["w1"] * np.float32(2.0 ** shift)
+    scaled["w2"] = scaled["w2"] * np.float32(2.0 ** -shift)
+    a = g.eval_steps(gen.config1(0, 3).with_heads(heads), counts=False)
+    b = g.eval_steps(gen.config1(0, 3).with_heads(dataclasses.replace(heads, storage=scaled)), counts=False)
+    for k in a:
+        np.testing.assert_array_equal(b[k], a[k], err_msg=k)
+
+
 # ------------------------------------------------------------- edge cases --
 def _wl(desc, n_steps, heads=None, tp=1, layers=1, specs=None):
     return gen.Workload("edge", desc, steprec(n_steps, layers=layers, hidden=64, tp=tp, n_launch=1),
