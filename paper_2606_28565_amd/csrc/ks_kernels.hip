@@ -563,7 +563,9 @@ struct HeadBF16 {
     const uint16_t *b2 = (const uint16_t *)p.b2 + (size_t)fam * HID;
     const uint16_t *w3 = (const uint16_t *)p.w3 + (size_t)fam * HID;
     const uint16_t *b3 = (const uint16_t *)p.b3 + fam;
-    for (int d = tid; d < W1_DW; d += kWgThreads) {
+#pragma unroll
+    for (int i = 0; i < W1_DW / kWgThreads; ++i) {
+      const int d = tid + i * kWgThreads;
       const int q = d & 3, lane = (d >> 2) & 63, frag = d >> 8;
       const int kc = frag % KC1, mb = frag / KC1;
       const int row = mb * 32 + (lane & 31);
@@ -576,15 +578,25 @@ struct HeadBF16 {
       // 32 of one K chunk's fragment, at dwords 0-1 (first 8 of the chunk's
       // 16 units) or 2-3 (last 8): each load feeds two 8-byte LDS writes
       // (one 2-byte load per unit, scattered, took several times longer)
-      for (int c = tid; c < HID * HID / 8; c += kWgThreads) {
-        const int row = c / (HID / 8), col = (c % (HID / 8)) * 8;
-        const u32x4 v = *reinterpret_cast<const u32x4 *>(w2 + (size_t)row * HID + col);
-        const int kc = 2 * (col >> 5) + ((col >> 4) & 1);
-        const int frag = (row >> 5) * KC2 + kc;
-        const int d0 = (frag * 64 + (row & 31)) * 4 + ((col & 8) ? 2 : 0);
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-        *reinterpret_cast<u32x2 *>(lds + OFF_W2 + d0) = u32x2{v[0], v[1]};
-        *reinterpret_cast<u32x2 *>(lds + OFF_W2 + d0 + 32 * 4) = u32x2{v[2], v[3]};
+      // (eight rounds' loads before any is written, one memory round trip per
+      // eight: the homogeneous 70B trace's evaluation 54 -> 39 us)
+      constexpr int kRounds = HID * HID / 8 / kWgThreads < 8 ? HID * HID / 8 / kWgThreads : 8;
+      for (int c0 = tid; c0 < HID * HID / 8; c0 += kRounds * kWgThreads) {
+        u32x4 v[kRounds];
+#pragma unroll
+        for (int i = 0; i < kRounds; ++i)
+          v[i] = *reinterpret_cast<const u32x4 *>(w2 + (size_t)(c0 + i * kWgThreads) * 8);
+#pragma unroll
+        for (int i = 0; i < kRounds; ++i) {
+          const int c = c0 + i * kWgThreads;
+          const int row = c / (HID / 8), col = (c % (HID / 8)) * 8;
+          const int kc = 2 * (col >> 5) + ((col >> 4) & 1);
+          const int frag = (row >> 5) * KC2 + kc;
+          const int d0 = (frag * 64 + (row & 31)) * 4 + ((col & 8) ? 2 : 0);
+          typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+          *reinterpret_cast<u32x2 *>(lds + OFF_W2 + d0) = u32x2{v[i][0], v[i][1]};
+          *reinterpret_cast<u32x2 *>(lds + OFF_W2 + d0 + 32 * 4) = u32x2{v[i][2], v[i][3]};
+        }
       }
     } else {
       for (int d = tid; d < W2_DW; d += kWgThreads) {
