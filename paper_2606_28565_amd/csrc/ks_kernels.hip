@@ -1935,16 +1935,27 @@ struct SRec {
   int tile;
 };
 
+// A family starts at any record, so its quads are 16-byte accesses at 4-byte
+// alignment, which global memory takes (a wave's access is contiguous; off
+// alignment it touches one more cache line).  One access per record for the
+// families off 16-byte alignment, nine of ten in a trace with an odd number of
+// steps, took 176 us where this takes 132 (t_kernel of 28.9M records for two
+// specs; 126 and 124 at 40,000 steps), all outputs for eight specs 251 and 175.
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // a lane's four consecutive records (4 lane .. 4 lane + 3 of the tile) of
 // one field array, base: the tile's first record: one 16-byte load when the
-// four are valid and the address is 16-byte aligned, else one load per
-// record with its index clamped to the tile's valid rows (nvalid >= 1).
+// four are valid, else one load per record with its index clamped to the
+// tile's valid rows (nvalid >= 1).
 // The 16-byte loads are non-temporal: every record is read once per call.
 __device__ __forceinline__ u32x4 load_quad(const uint32_t *base, int lane, int nvalid) {
   const uint32_t *q = reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(base) +
                                                          (uint32_t)(16 * lane));
-  if (kStreamR * lane + kStreamR - 1 < nvalid && (reinterpret_cast<uintptr_t>(q) & 15) == 0)
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(q));
+  if (kStreamR * lane + kStreamR - 1 < nvalid) {
+    const u32x4_any v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(q));
+    return u32x4{v[0], v[1], v[2], v[3]};
+  }
   u32x4 r;
 #pragma unroll
   for (int j = 0; j < kStreamR; ++j) {
@@ -1957,13 +1968,12 @@ __device__ __forceinline__ u32x4 load_quad(const uint32_t *base, int lane, int n
 // four consecutive per-pair values of a lane (records 4 lane .. 4 lane + 3
 // of the tile) at base + 4 lane (base: the tile's first record, the same
 // for the whole wave, so the lane's part is a 32-bit offset): one 16-byte
-// store (non-temporal: nothing here reads it back) when all four are valid
-// and the address is 16-byte aligned, else one store per valid record
+// store (non-temporal: nothing here reads it back) when all four are valid,
+// else one store per valid record
 __device__ __forceinline__ void store_quad(float *base, int lane, int nvalid, const float (&v)[kStreamR]) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
   float *q = reinterpret_cast<float *>(reinterpret_cast<char *>(base) + (uint32_t)(16 * lane));
-  if (kStreamR * lane + kStreamR - 1 < nvalid && (reinterpret_cast<uintptr_t>(q) & 15) == 0) {
-    __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4 *>(q));
+  if (kStreamR * lane + kStreamR - 1 < nvalid) {
+    __builtin_nontemporal_store(f32x4_any{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4_any *>(q));
   } else {
 #pragma unroll
     for (int j = 0; j < kStreamR; ++j)
