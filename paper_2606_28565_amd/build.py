@@ -44,14 +44,17 @@ def build(verbose: bool = False) -> str:
     os.makedirs(tmp, exist_ok=True)
     common = ["-I", INCLUDE, "-I", CSRC]
     jobs = []
-    for src in ("ks_kernels.hip", "ks_unique.hip", "ks_finish.hip", "ks_expand.hip", "ks_static.hip"):
-        jobs.append((src, [HIPCC, *DEVICE_FLAGS, *common]))
+    # the heads' instantiations of the evaluation kernel compile in parts
+    for heads in range(4):
+        jobs.append(("ks_kernels.hip", f"ks_kernels{heads}", [HIPCC, *DEVICE_FLAGS, *common, f"-DKS_HEADS={heads}"]))
+    for src in ("ks_unique.hip", "ks_finish.hip", "ks_expand.hip", "ks_static.hip"):
+        jobs.append((src, os.path.splitext(src)[0], [HIPCC, *DEVICE_FLAGS, *common]))
     for src in ("ks_api.cpp", "ks_sim.cpp"):
-        jobs.append((src, [HIPCC, *HOST_FLAGS, *common, "-D__HIP_PLATFORM_AMD__"]))
+        jobs.append((src, os.path.splitext(src)[0], [HIPCC, *HOST_FLAGS, *common, "-D__HIP_PLATFORM_AMD__"]))
 
     def compile_one(job):
-        src, cmd = job
-        obj = os.path.join(tmp, os.path.splitext(src)[0] + ".o")
+        src, name, cmd = job
+        obj = os.path.join(tmp, name + ".o")
         _run([*cmd, "-c", os.path.join(CSRC, src), "-o", obj])
         return obj
 

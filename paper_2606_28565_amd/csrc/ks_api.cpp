@@ -90,7 +90,7 @@ constexpr int kUniqOver = 15;
 
 struct UniqPlan {
   uint32_t mask = 0;
-  bool may_overflow = false;
+  bool rest = false;   // grouped GEMMs, or a family that might not fit
   int32_t chunk_off[KS_NFAM + 1];
   uint32_t chunk_entries[KS_NFAM], ent_off[KS_NFAM], base[KS_NFAM], cap[KS_NFAM];
   uint32_t slot_off[KS_NFAM], slots[KS_NFAM], slot_mask[KS_NFAM];
@@ -112,7 +112,7 @@ bool uniq_plan(const ks_desc *d, int32_t n_specs, UniqPlan *pl) {
     pl->chunk_entries[f] = flat ? ks::kUniqChunk : ks::kUniqChunk / 4;
     pl->cap[f] = (uint32_t)(flat || rows < room ? rows : room);
     if (rows > 0) pl->mask |= 1u << f;
-    pl->may_overflow = pl->may_overflow || !flat;
+    pl->rest = pl->rest || !flat || (f == KS_GROUPED_GEMM && d->fam_off[f + 1] > d->fam_off[f]);
     // the table: a slot per step for attention; for a dense family twice its
     // records, up to 2^15 (GEMMs, several kernels per layer, 2^18): a trace's
     // token counts are a few thousand, and a slot taken by another record
@@ -379,7 +379,6 @@ void fill_uniq(ks::UniqParams &u, ks::EvalParams &p, const ks_desc *d, const Uni
   u.a = p.a;
   u.mult = p.mult;
   u.n_steps = p.n_steps;
-  u.may_overflow = pl.may_overflow;
   u.ent = reinterpret_cast<ks::UniqEntry *>(ws + L.ent);
   u.dir = reinterpret_cast<uint32_t *>(ws + L.range);
   u.list = reinterpret_cast<uint32_t *>(ws + L.list);
@@ -388,6 +387,7 @@ void fill_uniq(ks::UniqParams &u, ks::EvalParams &p, const ks_desc *d, const Uni
   u.chunk_count = reinterpret_cast<uint32_t *>(ws + L.count);
   u.slot_row = reinterpret_cast<uint32_t *>(ws + L.rows);
   u.slot_id = reinterpret_cast<uint32_t *>(ws + L.slot);
+  u.rest = pl.rest;
   u.ent_slot = reinterpret_cast<uint32_t *>(u.ent + pl.entries);
   u.req_off = d->req_off;
   u.req_q = d->req_q;

@@ -68,7 +68,7 @@ struct UniqParams {
   uint32_t base[KS_NFAM], cap[KS_NFAM];
   uint32_t slot_off[KS_NFAM], slots[KS_NFAM], slot_mask[KS_NFAM];   // a family's table (attention: a slot per step)
   int32_t scan_off[KS_NFAM + 1], unit_off[KS_NFAM + 1];              // k_join's workgroups and waves
-  bool may_overflow;                   // host only: the entries or records of some family might not fit
+  bool rest;                           // host only: some records may be evaluated without it
   UniqEntry *ent;
   uint32_t *dir;        // [KS_NFAM][n_steps][2]: first entry + 1, end row (zero: no such records)
   uint32_t *list, *count, *over;
@@ -120,9 +120,8 @@ struct EvalParams {
   uint32_t *err;
   // the different records (k_unique), for the families of uniq_mask: k_eval's
   // unique-record variant evaluates u_list[u_base[f] + i], i < u_count[f], and
-  // stores t at u_t[(u_base[f] + i) n_specs + spec].  u_over (nullable): nonzero
-  // when they did not fit; that variant then does nothing, and a direct launch
-  // that has the pointer runs only then.
+  // stores t at u_t[(u_base[f] + i) n_specs + spec].  u_over: nonzero when they
+  // did not fit; that variant then evaluates every record.
   const UniqParams *uniq;      // host pointer, read by launch_eval only (nullptr: every record is evaluated)
   uint32_t uniq_mask;
   const uint32_t *u_list, *u_count, *u_over;

@@ -84,6 +84,7 @@ __device__ __forceinline__ void swap32(uint32_t &lo, uint32_t &hi) {
 // step) range table (an empty range marks a family without that step).
 __device__ void spec_prep_one(const ks_spec *__restrict__ specs, int s, SpecC *__restrict__ out, uint32_t *err);
 
+#if KS_HEADS == 0
 // With specs (n_specs > 0), the first workgroup also forms their constants
 // once the flag word is reset (a bad spec then flags the fresh word).
 __global__ void k_clear(uint32_t *err, uint32_t *range, int64_t n_range, const ks_spec *specs, int32_t n_specs,
@@ -105,6 +106,7 @@ __global__ void k_attn_agg(const uint32_t *__restrict__ req_off, const uint32_t 
   attn_agg(req_off, rq, rh, n_steps, n_req, agg, err, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
            (int64_t)gridDim.x * blockDim.x);
 }
+#endif
 
 // ------------------------------------------------------------ record counts
 struct Cnt {
@@ -284,6 +286,7 @@ __device__ __forceinline__ CntF record_counts_f(int fam, uint32_t m32, uint32_t 
   return c;
 }
 
+#if KS_HEADS == 0
 // ------------------------------------------------------------ spec constants
 __device__ void spec_prep_one(const ks_spec *__restrict__ specs, int s, SpecC *__restrict__ out, uint32_t *err) {
   const ks_spec sp = specs[s];
@@ -315,6 +318,7 @@ __global__ void k_spec_prep(const ks_spec *__restrict__ specs, int32_t n_specs, 
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s < n_specs) spec_prep_one(specs, s, out, err);
 }
+#endif
 
 // Spec constants through the scalar cache: they are read-only during the
 // evaluation kernel and the index is wave-uniform, so the load goes through
@@ -1378,7 +1382,9 @@ __device__ __forceinline__ Fields load_fields(const EvalParams &p, const Tile &t
   if (fam != KS_RMSNORM && fam != KS_SILU_MUL && fam != KS_EMBED) f.k = (p.k + r0)[off];
   if (grouped || attn) f.a = (p.a + r0)[off];
   if (grouped) f.b = (p.b + r0)[off];
-  if constexpr (MULT) f.mult = (float)(p.mult + r0)[off];   // exact below 2^24
+  if constexpr (MULT) {
+    if (p.mult) f.mult = (float)(p.mult + r0)[off];   // exact below 2^24
+  }
   const bool hp = t.row0 > t.fam_lo, hn = t.row0 + kTileRows < t.fam_hi;
   if constexpr (VEC) {
     // one vector load for both neighbours (each lane's address stays inside
@@ -1410,52 +1416,126 @@ __device__ __forceinline__ void tile_edges(const Tile &t, const Fields &f, uint3
 // Variants, each a separate instantiation so that the kernels without them
 // keep their registers and schedule: kVarGrid compiles Tier B routing in,
 // kVarMult weights each record's step-sum term by its multiplicity, kVarUniq
-// takes the different records k_unique found instead of all of them and
-// stores each one's t for every spec (no step sums, no per-pair outputs).
-enum : int { kVarGrid = 1, kVarMult = 2, kVarUniq = 4, kNumVars = 8 };
+// takes the different records k_unique found (each one's t for every spec is
+// stored, no step sums or per-pair outputs) and, with kVarRest, beside them
+// every record of the families left out (all families when the different
+// records did not fit): one launch, whose parts fill each other's last round
+// (MoE trace 61 -> 54 us), but the code of both (homogeneous 70B trace, where
+// nothing is left out: 46 us with it, 39 without).
+enum : int { kVarGrid = 1, kVarMult = 2, kVarUniq = 4, kVarRest = 2, kNumVars = 8 };
 
 // heads that take the software-pipelined spec loop
 template <class H, class = void> struct PipeOK : std::false_type {};
 template <class H> struct PipeOK<H, std::enable_if_t<H::kPipe>> : std::true_type {};
 
-// k_eval over the different records: their tiles per family (counted by
-// k_unique, so known on the device only) and the split of the spec loop that
-// fills the grid when the tiles alone do not.
+// How many ranges to split S specs into for `tiles` tiles on `grid` workgroups:
+// the fewest spec evaluations in a row (an item's setup counts for 0.8 of one),
+// over one to four rounds of the grid.  (As many ranges as fill the grid, a
+// remainder taking a second round, took 475 us where this takes 307, fp32 grid.)
+// spec_cost: that of k rounds (0: one range), and its ranges.
+__host__ __device__ inline uint32_t spec_cost(uint32_t tiles, uint32_t grid, uint32_t S, uint32_t k, uint32_t &ranges) {
+  ranges = 1;
+  uint32_t per = S;
+  if (k > 0 && tiles > 0) {
+    uint32_t c = k * grid / tiles;
+    c = c < 1 ? 1 : c < S ? c : S;
+    per = (S + c - 1) / c;
+    ranges = (S + per - 1) / per;
+  }
+  return (tiles * ranges + grid - 1) / grid * (5 * per + 4);
+}
+
+inline int spec_ranges(uint32_t tiles, uint32_t grid, uint32_t S) {
+  uint32_t best = 1, cost = ~0u;
+  for (uint32_t k = 0; k <= 4; ++k) {
+    uint32_t c, t = spec_cost(tiles, grid, S, k, c);
+    if (t < cost) cost = t, best = c;
+  }
+  return (int)best;
+}
+
+// The work of the unique-record variant, formed on the device (the different
+// records are counted there).  Items of different records are four (64-record
+// tile, spec range) pairs of one family, one per wave, so that a family's last
+// tiles do not leave waves idle; items of the other families' records are
+// workgroup tiles and spec ranges as without this variant.
 struct UniqTiles {
-  int wgt[KS_NFAM + 1], cnt[KS_NFAM];
-  int spec_chunk, n_chunks;
+  int wgt[KS_NFAM + 1], cnt[KS_NFAM], spec_chunk, n_chunks;   // different records
+  int d_wgt[KS_NFAM + 1], d_chunk, d_chunks;                  // every record
 };
 
+// By one wave: lane f has family f, and lanes 0 .. 4 and 8 .. 12 price the spec
+// ranges of the different records and of the others (one thread that did it all
+// took 5 to 10 us, with its divisions in a row).
 __device__ __forceinline__ void uniq_tiles(const EvalParams &p, int grid, UniqTiles &u) {
-  u.wgt[0] = 0;
-  for (int f = 0; f < KS_NFAM; ++f) {
-    const int c = (p.uniq_mask >> f) & 1u ? (int)min(p.u_count[f], p.u_cap[f]) : 0;
-    u.cnt[f] = c;
-    u.wgt[f + 1] = u.wgt[f] + (c + kWgRows - 1) / kWgRows;
+  const int lane = threadIdx.x & 63, f = lane < KS_NFAM ? lane : 0;
+  const uint32_t mask = p.u_over[0] ? 0u : p.uniq_mask;
+  const bool on = (mask >> f) & 1u;
+  const int cnt = lane < KS_NFAM && on ? (int)min(p.u_count[f], p.u_cap[f]) : 0;
+  const int t64 = (cnt + kTileRows - 1) / kTileRows;
+  int rest = lane < KS_NFAM && !on ? p.wgt_off[f + 1] - p.wgt_off[f] : 0, tiles = t64, all = rest;
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) {
+    tiles += __shfl_xor(tiles, off);
+    all += __shfl_xor(all, off);
   }
-  const int n = u.wgt[KS_NFAM];
-  u.spec_chunk = p.n_specs;
-  u.n_chunks = 1;
-  if (n > 0 && n < grid && p.n_specs > 1) {
-    const int chunks = min(max(grid / n, 1), p.n_specs);   // one item per workgroup, never a second round
-    u.spec_chunk = (p.n_specs + chunks - 1) / chunks;
-    u.n_chunks = (p.n_specs + u.spec_chunk - 1) / u.spec_chunk;
+  // (each family's last item of different records may be partly filled)
+  const bool other = lane >= 8;
+  const uint32_t n = other ? (uint32_t)all : (uint32_t)(tiles + kWgWaves - 1) / kWgWaves;
+  const uint32_t g = other ? (uint32_t)grid : (uint32_t)max(grid - KS_NFAM, 1);
+  uint32_t c = 1, cost = ~0u;
+  // four full rounds and more take one range (and the products below stay small)
+  if ((lane & 7) == 0 || ((lane & 7) <= 4 && n < 4 * g)) cost = spec_cost(n, g, (uint32_t)p.n_specs, lane & 7, c);
+#pragma unroll
+  for (int off = 1; off < 8; off <<= 1) {
+    const uint32_t c2 = __shfl_xor(c, off), t2 = __shfl_xor(cost, off);
+    if (t2 < cost || (t2 == cost && c2 < c)) cost = t2, c = c2;
+  }
+  const int cu = __builtin_amdgcn_readlane((int)c, 0), cd = __builtin_amdgcn_readlane((int)c, 8);
+  int items = (t64 * cu + kWgWaves - 1) / kWgWaves;
+  if (lane < KS_NFAM) u.cnt[lane] = cnt;
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) {
+    const int i2 = __shfl_up(items, off), r2 = __shfl_up(rest, off);
+    if (lane >= off) items += i2, rest += r2;
+  }
+  if (lane < KS_NFAM) {
+    u.wgt[lane + 1] = items;
+    u.d_wgt[lane + 1] = rest;
+  }
+  if (lane == 0) {
+    u.wgt[0] = u.d_wgt[0] = 0;
+    u.n_chunks = cu;
+    u.spec_chunk = (p.n_specs + cu - 1) / cu;
+    u.d_chunks = cd;
+    u.d_chunk = (p.n_specs + cd - 1) / cd;
   }
 }
 
-// tile wt of the different records: row0 counts them from the family's first
-__device__ __forceinline__ Tile locate_uniq(const UniqTiles &u, int wt, int wave, int fam0) {
+// item w of the different records, this wave's tile and spec range: row0 counts
+// the records from the family's first
+__device__ __forceinline__ Tile locate_uniq(const UniqTiles &u, int w, int wave, int &range) {
   Tile t;
-  int fam = fam0;
-  while (wt >= __builtin_amdgcn_readfirstlane(u.wgt[fam + 1])) ++fam;
+  int fam = 0;
+  while (w >= __builtin_amdgcn_readfirstlane(u.wgt[fam + 1])) ++fam;
+  const int i = (w - __builtin_amdgcn_readfirstlane(u.wgt[fam])) * kWgWaves + wave;
+  const int c = __builtin_amdgcn_readfirstlane(u.n_chunks);
   t.fam = fam;
-  t.tile_in_fam = (wt - __builtin_amdgcn_readfirstlane(u.wgt[fam])) * kWgWaves + wave;
+  t.tile_in_fam = c == 1 ? i : i / c;
+  range = c == 1 ? 0 : i % c;
   t.fam_lo = 0;
   t.fam_hi = __builtin_amdgcn_readfirstlane(u.cnt[fam]);
   t.row0 = (int64_t)t.tile_in_fam * kTileRows;
   const int64_t left = t.fam_hi - t.row0;
   t.nvalid = left <= 0 ? 0 : (left < kTileRows ? (int)left : kTileRows);
   return t;
+}
+
+// workgroup tile wt of the families whose every record is evaluated
+__device__ __forceinline__ Tile locate_rest(const EvalParams &p, const UniqTiles &u, int wt, int wave) {
+  int fam = 0;
+  while (wt >= __builtin_amdgcn_readfirstlane(u.d_wgt[fam + 1])) ++fam;
+  return locate(p, p.wgt_off[fam] + wt - __builtin_amdgcn_readfirstlane(u.d_wgt[fam]), wave, fam);
 }
 
 __device__ __forceinline__ Fields load_uniq(const EvalParams &p, const Tile &t, int lane) {
@@ -1480,14 +1560,16 @@ __device__ __forceinline__ Fields load_uniq(const EvalParams &p, const Tile &t, 
 // a tail lane stores its segment's sum to dst[s] (dst: the tile's carry
 // slots or the (family, step) partials, one per spec, contiguous), a record
 // of multiplicity m adding m t (one fp32 rounding).
-// (UNIQ: the record's t to u_dst[s] instead.)
-template <bool MULT, bool UNIQ>
+// (UNIQ: with u_dst, a different record's t to u_dst[s] instead.)
+template <bool MULT, bool UNIQ, bool REST>
 __device__ __forceinline__ void spec_tail(const EvalParams &p, int s, float t_roof, float eta, float t, bool valid,
                                           bool live, int64_t row, float tfac, const float (&fac)[6], double *dst,
                                           float *u_dst) {
   if constexpr (UNIQ) {
-    if (valid) u_dst[s] = t;
-    return;
+    if (!REST || u_dst) {
+      if (valid) u_dst[s] = t;
+      return;
+    }
   }
   // (the per-pair test first: a call without per-pair outputs forms no
   // address)
@@ -1520,8 +1602,9 @@ __device__ __forceinline__ int item_range(int w, int n) {
 template <int KIND, int VAR>
 __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalParams p) {
   constexpr bool GRID = (VAR & kVarGrid) != 0;
-  constexpr bool MULT = (VAR & kVarMult) != 0;
   constexpr bool UNIQ = (VAR & kVarUniq) != 0;
+  constexpr bool REST = !UNIQ || (VAR & kVarRest) != 0;
+  constexpr bool MULT = (VAR & kVarMult) != 0;   // (kVarRest: if there are any)
   using H = typename KindOf<KIND>::H;
   constexpr int IN = KindOf<KIND>::IN;
   __shared__ __align__(16) uint32_t lds[H::LDS_DW];   // 16-byte fragment reads, 8-byte staging writes
@@ -1530,37 +1613,23 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // work item w: workgroup tile w / n_chunks, specs [s0, s1) of range w % n_chunks
   int n_chunks = p.n_chunks, spec_chunk = p.spec_chunk;
-  int n_wgt = p.wgt_off[KS_NFAM];
+  int n_work = p.wgt_off[KS_NFAM] * n_chunks, n_uniq = 0;
   __shared__ UniqTiles ut;
   if constexpr (UNIQ) {
-    if (p.u_over[0]) return;   // the records did not fit: the direct launch takes them
-    if (threadIdx.x == 0) uniq_tiles(p, (int)gridDim.x, ut);
+    if (threadIdx.x < 64) uniq_tiles(p, (int)gridDim.x, ut);
     __syncthreads();
-    n_chunks = __builtin_amdgcn_readfirstlane(ut.n_chunks);
-    spec_chunk = __builtin_amdgcn_readfirstlane(ut.spec_chunk);
-    n_wgt = __builtin_amdgcn_readfirstlane(ut.wgt[KS_NFAM]);
-  } else if (p.u_over) {
-    if (!p.u_over[0]) return;   // the different records were evaluated instead
+    n_chunks = __builtin_amdgcn_readfirstlane(ut.d_chunks);
+    spec_chunk = __builtin_amdgcn_readfirstlane(ut.d_chunk);
+    n_work = __builtin_amdgcn_readfirstlane(ut.d_wgt[KS_NFAM]) * n_chunks;
+    n_uniq = __builtin_amdgcn_readfirstlane(ut.wgt[KS_NFAM]);
   }
-  const int n_work = n_wgt * n_chunks;
   // tiles without a head, and the heads that run one wave per SIMD, take
   // their neighbour steps by a vector load (the scalar loads' round trip is
   // waited for by the next scalar or LDS wait, which one wave per SIMD
   // cannot cover; with two waves per SIMD the vector load measured no
   // better overall)
   constexpr bool VEC = !H::kMlp || MinWg<KIND>::value == 1;
-  auto find = [&](int w, int fam0) {
-    if constexpr (UNIQ) return locate_uniq(ut, item_tile(w, n_chunks), wave, fam0);
-    else return locate(p, item_tile(w, n_chunks), wave, fam0);
-  };
-  auto fetch = [&](const Tile &t) {
-    if constexpr (UNIQ) return load_uniq(p, t, lane);
-    else return load_fields<MULT, VEC>(p, t, lane);
-  };
   int staged = -1;
-  // the next tile's fields are loaded while the current one is evaluated
-  Tile tn = {};
-  Fields fn = {0, 0, 0, 0, 0, 0, kNoKey, kNoKey, kNoKey, 1.0f};
   // With few work items per workgroup the heads take a contiguous range of
   // them, so that a workgroup meets one or two families and stages their
   // weights into LDS once or twice (striding over the grid it restaged them
@@ -1576,19 +1645,44 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
   const int w_end =
       blocked ? __builtin_amdgcn_readfirstlane(w_begin + n_work / G + (b < n_work % G ? 1 : 0)) : n_work;
   const int w_step = blocked ? 1 : G;
-  if (w_begin < w_end) {
-    tn = find(w_begin, 0);
-    fn = fetch(tn);
-  }
-  for (int w = w_begin; w < w_end; w += w_step) {
+  // The different records' items, after those: contiguous ranges from the last
+  // workgroup back (the first ones have the remainder of the others).
+  const int ub = G - 1 - b;
+  const int u_begin = UNIQ ? __builtin_amdgcn_readfirstlane(ub * (n_uniq / G) + min(ub, n_uniq % G)) : 0;
+  const int u_end = UNIQ ? __builtin_amdgcn_readfirstlane(u_begin + n_uniq / G + (ub < n_uniq % G ? 1 : 0)) : 0;
+  // the next tile's fields are loaded while the current one is evaluated
+  Tile tn = {};
+  Fields fn = {0, 0, 0, 0, 0, 0, kNoKey, kNoKey, kNoKey, 1.0f};
+  int range_n = 0;
+  bool uniq_n = false;
+  // item w of every record's, or (w at or past w_end) item u of the different ones
+  auto fetch = [&](int w, int u) {
+    uniq_n = false;
+    if (REST && w < w_end) {
+      range_n = item_range(w, n_chunks);
+      if constexpr (UNIQ) tn = locate_rest(p, ut, item_tile(w, n_chunks), wave);
+      else tn = locate(p, item_tile(w, n_chunks), wave, tn.fam);
+      fn = load_fields<MULT, VEC>(p, tn, lane);
+    } else if constexpr (UNIQ) {
+      if (u < u_end) {
+        uniq_n = true;
+        tn = locate_uniq(ut, u, wave, range_n);
+        fn = load_uniq(p, tn, lane);
+      }
+    }
+  };
+  fetch(w_begin, u_begin);
+  for (int w = w_begin, u = u_begin; (REST && w < w_end) || (UNIQ && u < u_end);) {
     const Tile tc = tn;
     const Fields fc = fn;
-    if (w + w_step < w_end) {
-      tn = find(w + w_step, tc.fam);
-      fn = fetch(tn);
-    }
-    const int s_lo = item_range(w, n_chunks) * spec_chunk;
-    const int s_hi = min(s_lo + spec_chunk, p.n_specs);
+    const int range = range_n;
+    const bool uq = UNIQ && (!REST || uniq_n);
+    if (REST && w < w_end) w += w_step;
+    else ++u;
+    fetch(w, u);
+    const int chunk = uq ? __builtin_amdgcn_readfirstlane(ut.spec_chunk) : spec_chunk;
+    const int s_lo = range * chunk;
+    const int s_hi = min(s_lo + chunk, p.n_specs);
     const int fam = tc.fam;
     // this family takes the bounded head (the plain eta = 1 stream has none)
     const bool bnd = KIND != kEtaOne && ((p.bounded_mask >> fam) & 1u);
@@ -1643,7 +1737,7 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
     float tfac = 0.0f;
     double *dst = nullptr;
     float *u_dst = nullptr;
-    if constexpr (UNIQ) {
+    if (uq) {
       u_dst = p.u_t + ((size_t)p.u_base[fam] + (size_t)tc.row0 + (size_t)(valid ? lane : 0)) * (size_t)p.n_specs;
     } else {
       // segment structure of this tile (spec-independent): keys are sorted
@@ -1730,7 +1824,7 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
             if constexpr (a.eta) eta_prev = 1.0f + __expf(-H::tail_reduce(zp, lds));
             if constexpr (a.tail) {
               if (s > 0)
-                spec_tail<MULT, UNIQ>(p, s_lo + s - 1, tr_prev, eta_prev, fmaxf(tr_prev * eta_prev, t0_prev), valid, live,
+                spec_tail<MULT, UNIQ, REST>(p, s_lo + s - 1, tr_prev, eta_prev, fmaxf(tr_prev * eta_prev, t0_prev), valid, live,
                                       row, tfac, fac, dst, u_dst);
             }
             if constexpr (NEXT && a.roof) on = small ? roofline<true>(rc, sn) : roofline<false>(rc, sn);
@@ -1767,7 +1861,7 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
         H::tail_pairs(st, zl, 0, 4);
         H::tail_pairs(st, zl, 4, 8);
         const float eta = 1.0f + __expf(-H::tail_reduce(zl, lds));
-        spec_tail<MULT, UNIQ>(p, s_lo + S - 1, tr_prev, eta, fmaxf(tr_prev * eta, t0_prev), valid, live, row, tfac,
+        spec_tail<MULT, UNIQ, REST>(p, s_lo + S - 1, tr_prev, eta, fmaxf(tr_prev * eta, t0_prev), valid, live, row, tfac,
                               fac, dst, u_dst);
         continue;
       }
@@ -1805,7 +1899,7 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
       if constexpr (GRID && !UNIQ) {
         if (valid && p.o_src) p.o_src[(size_t)s * (size_t)p.fam_off[KS_NFAM] + (size_t)row] = routed ? 2 : (bnd ? 1 : 0);
       }
-      spec_tail<MULT, UNIQ>(p, s, o.t_roof, eta, t, valid, live, row, tfac, fac, dst, u_dst);
+      spec_tail<MULT, UNIQ, REST>(p, s, o.t_roof, eta, t, valid, live, row, tfac, fac, dst, u_dst);
     }
   }
 }
@@ -2388,6 +2482,7 @@ void k_stream(EvalParams p) {
   static_assert(KS_EMBED == KS_NFAM - 1, "every family has its loop");
 }
 
+#if KS_HEADS == 0
 // ------------------------------------------------------------ eta source
 // Per pair, where eta came from when no grid routes any pair: 1 for the
 // families on the bounded head, 0 (the head of the mode) for the others.
@@ -2402,7 +2497,9 @@ __global__ void k_fill_source(uint8_t *src, EvalParams p) {
     src[i] = (uint8_t)((p.bounded_mask >> f) & 1u);
   }
 }
+#endif
 
+#if KS_HEADS == 0
 // ------------------------------------------------------------ validation
 __global__ void k_validate(ValidateParams p) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -2447,47 +2544,9 @@ __global__ void k_validate(ValidateParams p) {
   }
   if (bad) atomicOr(p.err, bad);
 }
+#endif
 
 // ------------------------------------------------------------ launchers
-static int grid_for(int64_t n, int block, int cap) {
-  int64_t g = (n + block - 1) / block;
-  if (g < 1) g = 1;
-  return (int)(g < cap ? g : cap);
-}
-
-hipError_t launch_clear(uint32_t *err, uint32_t *range, int64_t n_range, hipStream_t s) {
-  hipLaunchKernelGGL(k_clear, dim3(grid_for(n_range, 256, 2048)), dim3(256), 0, s, err, range, n_range,
-                     (const ks_spec *)nullptr, 0, (SpecC *)nullptr);
-  return hipGetLastError();
-}
-
-hipError_t launch_attn_agg(const uint32_t *req_off, const uint32_t *q, const uint32_t *h, int64_t n_steps,
-                           int64_t n_req, uint64_t *agg, uint32_t *err, hipStream_t s) {
-  if (n_steps == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_attn_agg, dim3(grid_for(n_steps, 256 / kAggLanes, 8192)), dim3(256), 0, s, req_off, q, h,
-                     n_steps, n_req, agg, err);
-  return hipGetLastError();
-}
-
-hipError_t launch_spec_prep(const ks_spec *specs, int32_t n_specs, SpecC *out, uint32_t *err, hipStream_t s) {
-  hipLaunchKernelGGL(k_spec_prep, dim3(grid_for(n_specs, 256, 4096)), dim3(256), 0, s, specs, n_specs, out, err);
-  return hipGetLastError();
-}
-
-// up to this many specs the clear kernel's first workgroup forms the spec
-// constants (one launch less); more take their own grid
-constexpr int32_t kFusedSpecs = 1024;
-
-hipError_t launch_clear_prep(uint32_t *err, uint32_t *range, int64_t n_range, const ks_spec *specs,
-                             int32_t n_specs, SpecC *out, hipStream_t s) {
-  const bool fused = n_specs <= kFusedSpecs;
-  hipLaunchKernelGGL(k_clear, dim3(grid_for(n_range, 256, 2048)), dim3(256), 0, s, err, range, n_range, specs,
-                     fused ? n_specs : 0, out);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || fused) return e;
-  return launch_spec_prep(specs, n_specs, out, err, s);
-}
-
 // The persistent grid: as many workgroups as are resident at once (the
 // occupancy the compiled kernel's registers and LDS allow, times the CU
 // count), so no workgroup of the head kinds waits for another to finish.
@@ -2530,15 +2589,131 @@ static hipError_t launch_grid(const EvalParams &p, hipStream_t s) {
   q.spec_chunk = p.n_specs;
   q.n_chunks = 1;
   if (n_wgt < cap && p.n_specs > 1) {
-    const int want = (cap + n_wgt - 1) / n_wgt;
-    const int chunks = want < p.n_specs ? want : p.n_specs;
-    q.spec_chunk = (p.n_specs + chunks - 1) / chunks;
-    q.n_chunks = (p.n_specs + q.spec_chunk - 1) / q.spec_chunk;
+    q.n_chunks = spec_ranges(n_wgt, cap, p.n_specs);
+    q.spec_chunk = (p.n_specs + q.n_chunks - 1) / q.n_chunks;
   }
   const int64_t work = (int64_t)n_wgt * q.n_chunks;
   const int grid = work < cap ? (int)work : cap;
   hipLaunchKernelGGL((k_eval<KIND, VAR>), dim3(grid), dim3(kWgThreads), 0, s, q);
   return hipGetLastError();
+}
+
+template <int KIND>
+hipError_t launch_kind(const EvalParams &p, hipStream_t s) {
+  // multiplicities matter only for the step sums
+  const bool mult = p.mult && p.partial;
+  if (p.grid_mask)
+    return mult ? launch_grid<KIND, kVarGrid | kVarMult>(p, s) : launch_grid<KIND, kVarGrid>(p, s);
+  return mult ? launch_grid<KIND, kVarMult>(p, s) : launch_grid<KIND, 0>(p, s);
+}
+
+template <int KIND, int VAR>
+static hipError_t launch_uniq_var(const EvalParams &p, hipStream_t s) {
+  int cap = 0;
+  const hipError_t e = resident_wgs<KIND, VAR>(&cap);
+  if (e != hipSuccess) return e;
+  // (how much work there is is known on the device only: workgroups without
+  // any leave at once)
+  const int64_t most = (int64_t)p.wgt_off[KS_NFAM] * p.n_specs;
+  hipLaunchKernelGGL((k_eval<KIND, VAR>), dim3((unsigned)(most < cap ? most : cap)), dim3(kWgThreads), 0, s, p);
+  return hipGetLastError();
+}
+
+template <int KIND>
+hipError_t launch_uniq(const EvalParams &p, hipStream_t s) {
+  if (p.uniq->rest)
+    return p.grid_mask ? launch_uniq_var<KIND, kVarUniq | kVarRest | kVarGrid>(p, s)
+                       : launch_uniq_var<KIND, kVarUniq | kVarRest>(p, s);
+  return p.grid_mask ? launch_uniq_var<KIND, kVarUniq | kVarGrid>(p, s) : launch_uniq_var<KIND, kVarUniq>(p, s);
+}
+
+// This file is compiled once per KS_HEADS (in parallel): 1 the fp32 heads, 2 the
+// bf16 heads up to hidden 128, 3 those of 256, 0 everything else.
+#if KS_HEADS == 1
+template hipError_t launch_kind<kF32_16_64>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kF32_16_64>(const EvalParams &, hipStream_t);
+template hipError_t launch_kind<kF32_16_128>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kF32_16_128>(const EvalParams &, hipStream_t);
+template hipError_t launch_kind<kF32_32_64>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kF32_32_64>(const EvalParams &, hipStream_t);
+template hipError_t launch_kind<kF32_32_128>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kF32_32_128>(const EvalParams &, hipStream_t);
+#endif
+#if KS_HEADS == 2
+template hipError_t launch_kind<kBF16_16_64>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kBF16_16_64>(const EvalParams &, hipStream_t);
+template hipError_t launch_kind<kBF16_16_128>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kBF16_16_128>(const EvalParams &, hipStream_t);
+template hipError_t launch_kind<kBF16_32_64>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kBF16_32_64>(const EvalParams &, hipStream_t);
+template hipError_t launch_kind<kBF16_32_128>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kBF16_32_128>(const EvalParams &, hipStream_t);
+#endif
+#if KS_HEADS == 3
+template hipError_t launch_kind<kBF16_16_256>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kBF16_16_256>(const EvalParams &, hipStream_t);
+template hipError_t launch_kind<kBF16_32_256>(const EvalParams &, hipStream_t);
+template hipError_t launch_uniq<kBF16_32_256>(const EvalParams &, hipStream_t);
+#endif
+#if KS_HEADS == 0
+extern template hipError_t launch_kind<kF32_16_64>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kF32_16_64>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_kind<kF32_16_128>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kF32_16_128>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_kind<kF32_32_64>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kF32_32_64>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_kind<kF32_32_128>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kF32_32_128>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_kind<kBF16_16_64>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kBF16_16_64>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_kind<kBF16_16_128>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kBF16_16_128>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_kind<kBF16_32_64>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kBF16_32_64>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_kind<kBF16_32_128>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kBF16_32_128>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_kind<kBF16_16_256>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kBF16_16_256>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_kind<kBF16_32_256>(const EvalParams &, hipStream_t);
+extern template hipError_t launch_uniq<kBF16_32_256>(const EvalParams &, hipStream_t);
+
+static int grid_for(int64_t n, int block, int cap) {
+  int64_t g = (n + block - 1) / block;
+  if (g < 1) g = 1;
+  return (int)(g < cap ? g : cap);
+}
+
+hipError_t launch_clear(uint32_t *err, uint32_t *range, int64_t n_range, hipStream_t s) {
+  hipLaunchKernelGGL(k_clear, dim3(grid_for(n_range, 256, 2048)), dim3(256), 0, s, err, range, n_range,
+                     (const ks_spec *)nullptr, 0, (SpecC *)nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_attn_agg(const uint32_t *req_off, const uint32_t *q, const uint32_t *h, int64_t n_steps,
+                           int64_t n_req, uint64_t *agg, uint32_t *err, hipStream_t s) {
+  if (n_steps == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_attn_agg, dim3(grid_for(n_steps, 256 / kAggLanes, 8192)), dim3(256), 0, s, req_off, q, h,
+                     n_steps, n_req, agg, err);
+  return hipGetLastError();
+}
+
+hipError_t launch_spec_prep(const ks_spec *specs, int32_t n_specs, SpecC *out, uint32_t *err, hipStream_t s) {
+  hipLaunchKernelGGL(k_spec_prep, dim3(grid_for(n_specs, 256, 4096)), dim3(256), 0, s, specs, n_specs, out, err);
+  return hipGetLastError();
+}
+
+// up to this many specs the clear kernel's first workgroup forms the spec
+// constants (one launch less); more take their own grid
+constexpr int32_t kFusedSpecs = 1024;
+
+hipError_t launch_clear_prep(uint32_t *err, uint32_t *range, int64_t n_range, const ks_spec *specs,
+                             int32_t n_specs, SpecC *out, hipStream_t s) {
+  const bool fused = n_specs <= kFusedSpecs;
+  hipLaunchKernelGGL(k_clear, dim3(grid_for(n_range, 256, 2048)), dim3(256), 0, s, err, range, n_range, specs,
+                     fused ? n_specs : 0, out);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || fused) return e;
+  return launch_spec_prep(specs, n_specs, out, err, s);
 }
 
 // k_stream: every eta = 1 evaluation (per-pair outputs and/or step sums,
@@ -2578,9 +2753,6 @@ static hipError_t launch_stream(const EvalParams &p, hipStream_t s) {
 }
 
 // eta = 1 (no bounded or grid family: those select the head-less kind)
-template <int KIND>
-static hipError_t launch_kind(const EvalParams &p, hipStream_t s);
-
 static hipError_t launch_eta_one(const EvalParams &p, hipStream_t s) {
   if (p.grid_mask || p.bounded_mask) return hipErrorInvalidValue;
   // the stream addresses the sum slots by 32-bit offsets from the partials:
@@ -2623,15 +2795,6 @@ static hipError_t launch_bounded_stream(const EvalParams &p, hipStream_t s) {
   return pair ? launch_stream<B | kStrSums | kStrPair>(p, s) : launch_stream<B | kStrSums>(p, s);
 }
 
-template <int KIND>
-static hipError_t launch_kind(const EvalParams &p, hipStream_t s) {
-  // multiplicities matter only for the step sums
-  const bool mult = p.mult && p.partial;
-  if (p.grid_mask)
-    return mult ? launch_grid<KIND, kVarGrid | kVarMult>(p, s) : launch_grid<KIND, kVarGrid>(p, s);
-  return mult ? launch_grid<KIND, kVarMult>(p, s) : launch_grid<KIND, 0>(p, s);
-}
-
 static hipError_t launch_direct(int kind, const EvalParams &p, hipStream_t s) {
   if (p.wgt_off[KS_NFAM] == 0) return hipSuccess;
   switch (kind) {
@@ -2651,26 +2814,6 @@ static hipError_t launch_direct(int kind, const EvalParams &p, hipStream_t s) {
   }
 }
 
-template <int KIND, int VAR>
-static hipError_t launch_uniq_grid(const EvalParams &p, hipStream_t s) {
-  int cap = 0;
-  const hipError_t e = resident_wgs<KIND, VAR>(&cap);
-  if (e != hipSuccess) return e;
-  // (how many tiles there are is known on the device only: k_eval splits the
-  // spec loop by itself, and workgroups without work leave at once)
-  int64_t most = 0;
-  for (int f = 0; f < KS_NFAM; ++f)
-    if ((p.uniq_mask >> f) & 1u) most += (p.u_cap[f] + kWgRows - 1) / kWgRows;
-  most *= p.n_specs;
-  hipLaunchKernelGGL((k_eval<KIND, VAR>), dim3((int)(most < cap ? most : cap)), dim3(kWgThreads), 0, s, p);
-  return hipGetLastError();
-}
-
-template <int KIND>
-static hipError_t launch_uniq(const EvalParams &p, hipStream_t s) {
-  return p.grid_mask ? launch_uniq_grid<KIND, kVarUniq | kVarGrid>(p, s) : launch_uniq_grid<KIND, kVarUniq>(p, s);
-}
-
 static hipError_t launch_uniq_kind(int kind, const EvalParams &p, hipStream_t s) {
   switch (kind) {
     case kF32_16_64: return launch_uniq<kF32_16_64>(p, s);
@@ -2687,27 +2830,10 @@ static hipError_t launch_uniq_kind(int kind, const EvalParams &p, hipStream_t s)
   }
 }
 
-// p restricted to the families of `mask` (their work; the tile numbers of the
-// carries stay those of the whole call)
-static EvalParams families_of(const EvalParams &p, uint32_t mask) {
-  EvalParams q = p;
-  q.wgt_off[0] = 0;
-  for (int f = 0; f < KS_NFAM; ++f)
-    q.wgt_off[f + 1] = q.wgt_off[f] + ((mask >> f) & 1u ? p.wgt_off[f + 1] - p.wgt_off[f] : 0);
-  return q;
-}
-
 hipError_t launch_eval(int kind, const EvalParams &p, hipStream_t s) {
   if (!p.uniq) return launch_direct(kind, p, s);
-  hipError_t e = launch_unique(*p.uniq, s);
-  if (e == hipSuccess) e = launch_uniq_kind(kind, p, s);
-  // the families it leaves out, then (each workgroup returning at once unless
-  // the different records did not fit) the others, every record
-  EvalParams q = families_of(p, ~p.uniq_mask);
-  q.u_over = nullptr;
-  if (e == hipSuccess) e = launch_direct(kind, q, s);
-  if (e == hipSuccess && p.uniq->may_overflow) e = launch_direct(kind, families_of(p, p.uniq_mask), s);
-  return e;
+  const hipError_t e = launch_unique(*p.uniq, s);
+  return e != hipSuccess ? e : launch_uniq_kind(kind, p, s);
 }
 
 hipError_t launch_fill_source(const EvalParams &p, hipStream_t s) {
@@ -2721,5 +2847,7 @@ hipError_t launch_validate(const ValidateParams &p, hipStream_t s) {
   hipLaunchKernelGGL(k_validate, dim3(1024), dim3(256), 0, s, p);
   return hipGetLastError();
 }
+
+#endif  // KS_HEADS == 0
 
 }  // namespace ks
