@@ -245,6 +245,15 @@ hipError_t launch_attn_agg(const uint32_t *req_off, const uint32_t *q, const uin
                            hipStream_t s);
 // k_unique and k_join
 hipError_t launch_unique(const UniqParams &p, hipStream_t s);
+// launch_clear_prep and launch_attn_agg in one launch, for at most kPrologueSteps
+// steps and kPrologueSpecs specs.  (Weak: a host build that stands in for those
+// two alone has none.)
+constexpr int64_t kPrologueSteps = 128;
+constexpr int32_t kPrologueSpecs = 1024;
+__attribute__((weak)) hipError_t launch_prologue(uint32_t *err, uint32_t *range, int64_t n_range, const ks_spec *specs,
+                                                 int32_t n_specs, SpecC *out, const uint32_t *req_off, const uint32_t *q,
+                                                 const uint32_t *h, int64_t n_steps, int64_t n_req, uint64_t *agg,
+                                                 hipStream_t s);
 // the evaluation of a kind's records; with p.uniq, through the different
 // records of its families
 hipError_t launch_eval(int kind, const EvalParams &p, hipStream_t s);
