@@ -66,16 +66,20 @@ constexpr size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 //   list    : uint32 per different record: its row
 //   ent     : 8 B per entry, then uint32 per entry: its slot
 //   ut      : n_specs float per different record
+// and for calls with per-pair outputs:
+//   ut      : two more of that size (t_roof, eta)
+//   entry   : uint16 per row of a chunk
 struct Layout {
   size_t specc, agg, range, partial, carry, base;   // base: without the different records
-  size_t ctl, rows, slot, count, list, ent, ut, total;     // total = base without them
+  size_t ctl, rows, slot, count, list, ent, ut, sums;      // sums: with them, for step sums
+  size_t entry, total;                                    // total: and per-pair outputs (base without them)
 };
 
 // The head work of every record from which finding the different ones pays:
-// 20 us at the rate the heads reach on the whole chip (fp32 70 TFLOP/s, bf16
+// 20 us at the rate the heads reach on the whole chip (fp32 140 TFLOP/s, bf16
 // 1.2 PFLOP/s).  Below it the two more kernels (8 us each at any size) cost
 // more than the evaluation.
-constexpr double kUniqF32Flops = 1.4e9, kUniqBf16Flops = 2.4e10;
+constexpr double kUniqF32Flops = 2.8e9, kUniqBf16Flops = 2.4e10;
 // (pairs of records and spec vectors that no head turns into that much work)
 constexpr double kUniqPairs = kUniqF32Flops / (2.0 * 128 * (32 + 128));
 
@@ -199,7 +203,11 @@ Layout layout_of(const ks_desc *d, int32_t n_specs, const UniqPlan *pl = nullptr
     L.ent = off;
     off += align256((size_t)pl->entries * (sizeof(ks::UniqEntry) + sizeof(uint32_t)));
     L.ut = off;
-    off += align256((size_t)pl->records * (size_t)n_specs * sizeof(float));
+    const size_t each = align256((size_t)pl->records * (size_t)n_specs * sizeof(float));
+    L.sums = off + each;
+    off += 3 * each;
+    L.entry = off;
+    off += align256((size_t)pl->chunk_off[KS_NFAM] * ks::kUniqChunk * sizeof(uint16_t));
   }
   L.total = off;
   return L;
@@ -354,24 +362,32 @@ void fill_eval(ks::EvalParams &p, const ks_desc *d, const ks_spec *specs, int32_
   p.err = reinterpret_cast<uint32_t *>(ws);
 }
 
-// Whether a call evaluates only its different records: step sums of MLP heads
-// without per-pair outputs, given the workspace for it, and enough head work.
+// Whether a call evaluates only its different records: MLP heads, given the
+// workspace for it, and enough head work; twice as much with per-pair outputs,
+// which one or two more kernels spread.  (Their sources come with the direct
+// evaluation of a grid.)
 bool takes_uniq(const ks_desc *d, int32_t n_specs, const ks_heads *h, int kind, const ks_kernel_out *kout,
-                size_t ws_bytes, UniqPlan *pl, Layout *L) {
+                size_t ws_bytes, UniqPlan *pl, Layout *L, bool *pair) {
   if (kind == ks::kEtaOne || kind == ks::kBoundedOnly || d->n_rows == 0) return false;
-  if (kout && (kout->flops || kout->bytes || kout->blocks || kout->t_roof || kout->eta || kout->t_kernel || kout->source))
-    return false;
+  *pair = kout && (kout->t_roof || kout->eta || kout->t_kernel);
+  const bool out = kout && (*pair || kout->flops || kout->bytes || kout->blocks);
+  if (kout && kout->source && h->grid_mask) return false;
   const double flops = 2.0 * (double)d->n_rows * n_specs * h->hidden * (h->in_dim + h->hidden);
-  if (flops < (h->precision == KS_F32 ? kUniqF32Flops : kUniqBf16Flops)) return false;
+  if (flops < (out ? 2.0 : 1.0) * (h->precision == KS_F32 ? kUniqF32Flops : kUniqBf16Flops)) return false;
   if (!uniq_plan(d, n_specs, pl)) return false;
   const Layout full = layout_of(d, n_specs, pl);
-  if (ws_bytes < full.total) return false;
+  if (ws_bytes < (*pair ? full.total : full.sums)) return false;
   *L = full;
   return true;
 }
 
-void fill_uniq(ks::UniqParams &u, ks::EvalParams &p, const ks_desc *d, const UniqPlan &pl, char *ws, const Layout &L) {
+void fill_uniq(ks::UniqParams &u, ks::EvalParams &p, const ks_desc *d, int32_t n_specs, const UniqPlan &pl, char *ws,
+               const Layout &L, bool pair) {
   std::memset(&u, 0, sizeof u);
+  u.pair = pair;
+  u.row_entry = reinterpret_cast<uint16_t *>(ws + L.entry);
+  p.u_pair = pair ? align256((size_t)pl.records * (size_t)n_specs * sizeof(float)) / sizeof(float) : 0;
+  p.uniq = &u;
   u.step = p.step;
   u.m = p.m;
   u.n = p.n;
@@ -387,7 +403,7 @@ void fill_uniq(ks::UniqParams &u, ks::EvalParams &p, const ks_desc *d, const Uni
   u.chunk_count = reinterpret_cast<uint32_t *>(ws + L.count);
   u.slot_row = reinterpret_cast<uint32_t *>(ws + L.rows);
   u.slot_id = reinterpret_cast<uint32_t *>(ws + L.slot);
-  u.rest = pl.rest;
+  u.rest = pl.rest || pair;
   u.ent_slot = reinterpret_cast<uint32_t *>(u.ent + pl.entries);
   u.req_off = d->req_off;
   u.req_q = d->req_q;
@@ -607,10 +623,15 @@ ks_status ks_eval_kernels(const ks_desc *desc, const ks_spec *specs, int32_t n_s
   if (st != KS_OK) return st;
   if (!out) return fail(KS_EINVAL, "out is NULL");
   char *w = static_cast<char *>(ws);
-  st = prologue(desc, specs, n_specs, w, L, false, stream);
+  UniqPlan pl;
+  bool pair = false;
+  const bool uniq = takes_uniq(desc, n_specs, heads, kind, out, ws_bytes, &pl, &L, &pair);
+  st = prologue(desc, specs, n_specs, w, L, false, stream, uniq);
   if (st != KS_OK) return st;
   ks::EvalParams p;
   fill_eval(p, desc, specs, n_specs, heads, out, w, L);
+  ks::UniqParams u;
+  if (uniq) fill_uniq(u, p, desc, n_specs, pl, w, L, pair);
   hipError_t e = timed_eval(kind, p, stream);
   if (e != hipSuccess) return hip_fail(e, "evaluation launch");
   return KS_OK;
@@ -637,16 +658,14 @@ static ks_status eval_steps_impl(const ks_desc *desc, const ks_steps *steps, con
     return fail(KS_EINVAL, "a step output is NULL");
   char *w = static_cast<char *>(ws);
   UniqPlan pl;
-  const bool uniq = takes_uniq(desc, n_specs, heads, kind, kout, ws_bytes, &pl, &L);
+  bool pair = false;
+  const bool uniq = takes_uniq(desc, n_specs, heads, kind, kout, ws_bytes, &pl, &L, &pair);
   st = prologue(desc, specs, n_specs, w, L, true, stream, uniq);
   if (st != KS_OK) return st;
   ks::EvalParams p;
   fill_eval(p, desc, specs, n_specs, heads, kout, w, L);
   ks::UniqParams u;
-  if (uniq) {
-    fill_uniq(u, p, desc, pl, w, L);
-    p.uniq = &u;
-  }
+  if (uniq) fill_uniq(u, p, desc, n_specs, pl, w, L, pair);
   p.partial = reinterpret_cast<double *>(w + L.partial);
   p.carry = reinterpret_cast<double *>(w + L.carry);
   p.range = reinterpret_cast<uint32_t *>(w + L.range);

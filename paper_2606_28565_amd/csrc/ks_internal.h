@@ -68,6 +68,9 @@ struct UniqParams {
   uint32_t base[KS_NFAM], cap[KS_NFAM];
   uint32_t slot_off[KS_NFAM], slots[KS_NFAM], slot_mask[KS_NFAM];   // a family's table (attention: a slot per step)
   int32_t scan_off[KS_NFAM + 1], unit_off[KS_NFAM + 1];              // k_join's workgroups and waves
+  bool pair;                           // per-pair outputs: note each row's entry, and take no record whose step is
+                                       // out of range (every record is evaluated then)
+  uint16_t *row_entry;                 // [chunks][kUniqChunk], with pair
   bool rest;                           // host only: some records may be evaluated without it
   UniqEntry *ent;
   uint32_t *dir;        // [KS_NFAM][n_steps][2]: first entry + 1, end row (zero: no such records)
@@ -127,6 +130,7 @@ struct EvalParams {
   const uint32_t *u_list, *u_count, *u_over;
   uint32_t u_base[KS_NFAM], u_cap[KS_NFAM];
   float *u_t;
+  size_t u_pair;     // nonzero: their t_roof and eta too, this and twice this many floats past t
   uint8_t *o_src;    // per pair: 0 head of the mode, 1 bounded head, 2 grid (nullable)
 };
 
@@ -245,6 +249,8 @@ hipError_t launch_attn_agg(const uint32_t *req_off, const uint32_t *q, const uin
                            hipStream_t s);
 // k_unique and k_join
 hipError_t launch_unique(const UniqParams &p, hipStream_t s);
+// the different records' per-pair values to every record's outputs
+hipError_t launch_spread(const UniqParams &u, const EvalParams &p, hipStream_t s);
 // launch_clear_prep and launch_attn_agg in one launch, for at most kPrologueSteps
 // steps and kPrologueSpecs specs.  (Weak: a host build that stands in for those
 // two alone has none.)

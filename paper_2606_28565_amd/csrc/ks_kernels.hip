@@ -1584,7 +1584,13 @@ __device__ __forceinline__ void spec_tail(const EvalParams &p, int s, float t_ro
                                           float *u_dst) {
   if constexpr (UNIQ) {
     if (!REST || u_dst) {
-      if (valid) u_dst[s] = t;
+      if (valid) {
+        u_dst[s] = t;
+        if (p.u_pair) {
+          u_dst[p.u_pair + s] = t_roof;
+          u_dst[2 * p.u_pair + s] = eta;
+        }
+      }
       return;
     }
   }
@@ -1734,12 +1740,12 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
     // written: no 64-bit products or 64-bit to float conversions.  Calls
     // with a measured grid keep the exact path, so that a record's cell is
     // the one the exact features give.
-    if (!GRID && (UNIQ || (!p.o_flops && !p.o_bytes && !p.o_blocks))) {
+    if (!GRID && !p.o_flops && !p.o_bytes && !p.o_blocks) {
       const CntF cf = record_counts_f(fam, fc.m, fc.n, fc.k, fc.a, fc.b, fc.st, p, bad);
       rc = row_consts(cf.B, cf.F, cf.Bt, cf.M, fc.n, fc.k);
     } else {
       const Cnt c = record_counts(fam, fc.m, fc.n, fc.k, fc.a, fc.b, fc.st, p, bad);
-      if (!UNIQ && valid) {
+      if (!uq && valid) {
         if (p.o_flops) p.o_flops[row] = c.F;
         if (p.o_bytes) p.o_bytes[row] = c.Bt;
         if (p.o_blocks) p.o_blocks[row] = c.B;
@@ -2500,6 +2506,26 @@ void k_stream(EvalParams p) {
 }
 
 #if KS_HEADS == 0
+// ------------------------------------------------------------ record counts
+// The exact counts of the records whose latency another record's evaluation
+// gave (the families of uniq_mask): HBM-bound, a row per thread.
+__global__ void k_counts(EvalParams p) {
+  if (p.u_over[0]) return;
+  const int64_t n_rows = p.fam_off[KS_NFAM];
+  int f = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * blockDim.x) {
+    while (i >= p.fam_off[f + 1]) ++f;
+    if (!((p.uniq_mask >> f) & 1u)) continue;
+    const bool attn = f == KS_ATTN_PREFILL || f == KS_ATTN_DECODE;
+    uint32_t bad = 0;
+    const Cnt c = record_counts(f, attn ? 0u : p.m[i], p.n[i], uses_k(f) ? p.k[i] : 0u, attn ? p.a[i] : 0u, 0u,
+                                attn ? p.step[i] : 0u, p, bad);
+    if (p.o_flops) p.o_flops[i] = c.F;
+    if (p.o_bytes) p.o_bytes[i] = c.Bt;
+    if (p.o_blocks) p.o_blocks[i] = c.B;
+  }
+}
+
 // ------------------------------------------------------------ eta source
 // Per pair, where eta came from when no grid routes any pair: 1 for the
 // families on the bounded head, 0 (the head of the mode) for the others.
@@ -2857,8 +2883,14 @@ static hipError_t launch_uniq_kind(int kind, const EvalParams &p, hipStream_t s)
 
 hipError_t launch_eval(int kind, const EvalParams &p, hipStream_t s) {
   if (!p.uniq) return launch_direct(kind, p, s);
-  const hipError_t e = launch_unique(*p.uniq, s);
-  return e != hipSuccess ? e : launch_uniq_kind(kind, p, s);
+  hipError_t e = launch_unique(*p.uniq, s);
+  if (e == hipSuccess) e = launch_uniq_kind(kind, p, s);
+  if (e == hipSuccess && p.uniq->pair) e = launch_spread(*p.uniq, p, s);
+  if (e == hipSuccess && (p.o_flops || p.o_bytes || p.o_blocks)) {
+    hipLaunchKernelGGL(k_counts, dim3(grid_for(p.fam_off[KS_NFAM], 256, 8192)), dim3(256), 0, s, p);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 hipError_t launch_fill_source(const EvalParams &p, hipStream_t s) {

@@ -193,7 +193,10 @@ __global__ __launch_bounds__(kUqThreads) __attribute__((amdgpu_waves_per_eu(8)))
     if (in && (int64_t)st[j] >= p.n_steps) flag = kErrStep;
     else if (end) p.dir[2 * ((size_t)f * (size_t)p.n_steps + st[j]) + 1] = (uint32_t)(row0 + r + 1);
   }
-  if (flag) atomicOr(p.err, flag);
+  if (flag) {
+    atomicOr(p.err, flag);
+    if (p.pair) p.over[0] = 1u;
+  }
   uint32_t piece = 0;
   {
     uint32_t all = 0;
@@ -265,6 +268,18 @@ __global__ __launch_bounds__(kUqThreads) __attribute__((amdgpu_waves_per_eu(8)))
     p.chunk_count[c] = n_ent;
   }
   __syncthreads();
+  if (p.pair) {
+    // each row's entry: the same place in its piece's first period
+    uint32_t t = piece0;
+    uint16_t e[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      t += (heads >> j) & 1u;
+      const uint32_t i = 4 * tid + j;
+      e[j] = (int)i < n ? (uint16_t)(sh.ent_of[t - 1] + (i - sh.start_of[t - 1]) % sh.bad_of[t - 1]) : 0;
+    }
+    *reinterpret_cast<ushort4 *>(p.row_entry + (size_t)c * kUniqChunk + 4 * tid) = ushort4{e[0], e[1], e[2], e[3]};
+  }
   // the directory's first entry, where the (family, step)'s global first record is
   {
     uint32_t t = piece0;
@@ -364,6 +379,71 @@ __global__ __launch_bounds__(kUqThreads) void k_join(UniqParams p) {
     }
     p.ent[ent0 + e].id = id;
   }
+}
+
+// Per-pair outputs of a chunk's rows: its entries' records in LDS, then for each
+// spec of the workgroup's range the rows' values, four consecutive rows per
+// thread, gathered from the different records' (a wave's rows share few) and
+// written as one 16-byte store.  Bound by the writes.
+__global__ __launch_bounds__(kUqThreads) void k_spread(UniqParams u, const float *ut, size_t pair, int32_t n_specs,
+                                                       int64_t n_rows, float *o_troof, float *o_eta, float *o_t,
+                                                       uint32_t total, uint32_t all_slots, int per_range) {
+  __shared__ uint32_t rec[kUniqChunk];
+  if (u.over[0]) return;   // every record was evaluated
+  typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+  const int tid = threadIdx.x, c = (int)blockIdx.x;
+  int f = 0;
+  while (c >= u.chunk_off[f + 1]) ++f;
+  const int64_t row0 = u.fam_off[f] + (int64_t)(c - u.chunk_off[f]) * kUniqChunk;
+  const int64_t left = u.fam_off[f + 1] - row0;
+  const int n = left < kUniqChunk ? (int)left : kUniqChunk;
+  const uint32_t ent0 = u.ent_off[f] + (uint32_t)(c - u.chunk_off[f]) * u.chunk_entries[f];
+  const uint32_t n_ent = min(u.chunk_count[c], u.chunk_entries[f]);
+  const ushort4 e = *reinterpret_cast<const ushort4 *>(u.row_entry + (size_t)c * kUniqChunk + 4 * tid);
+  for (uint32_t i = tid; i < n_ent; i += kUqThreads) {
+    const uint32_t id = u.ent[ent0 + i].id;
+    uint32_t r = id & kUniqIndex;
+    if (id & kUniqSlot) r = u.slot_id[min(r, all_slots - 1)];
+    rec[i] = min(r, total - 1);
+  }
+  __syncthreads();
+  if (4 * tid >= n) return;
+  const size_t S = (size_t)n_specs;
+  const float *src[4] = {ut + rec[e.x] * S, ut + rec[e.y] * S, ut + rec[e.z] * S, ut + rec[e.w] * S};
+  const int s0 = (int)blockIdx.y * per_range, s1 = min(s0 + per_range, n_specs);
+  auto copy = [&](float *out, size_t off) {
+    for (int s = s0; s < s1; ++s) {
+      float *q = out + (size_t)s * (size_t)n_rows + (size_t)row0 + 4 * tid;
+      float v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = src[j][off + s];
+      if (4 * tid + 3 < n) {
+        __builtin_nontemporal_store(f32x4_any{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4_any *>(q));
+      } else {
+        for (int j = 0; 4 * tid + j < n; ++j) q[j] = v[j];
+      }
+    }
+  };
+  if (o_t) copy(o_t, 0);
+  if (o_troof) copy(o_troof, pair);
+  if (o_eta) copy(o_eta, 2 * pair);
+}
+
+hipError_t launch_spread(const UniqParams &u, const EvalParams &p, hipStream_t s) {
+  const int chunks = u.chunk_off[KS_NFAM];
+  if (chunks == 0 || !(p.o_troof || p.o_eta || p.o_t)) return hipSuccess;
+  // spec ranges until about eight workgroups per CU (256) are at work
+  int ranges = 2048 / chunks;
+  ranges = ranges < 1 ? 1 : ranges > p.n_specs ? p.n_specs : ranges;
+  const int per = (p.n_specs + ranges - 1) / ranges;
+  uint32_t total = 0, slots = 0;
+  for (int f = 0; f < KS_NFAM; ++f) {
+    total = u.base[f] + u.cap[f] > total ? u.base[f] + u.cap[f] : total;
+    slots = u.slot_off[f] + u.slots[f] > slots ? u.slot_off[f] + u.slots[f] : slots;
+  }
+  hipLaunchKernelGGL(k_spread, dim3(chunks, (p.n_specs + per - 1) / per), dim3(kUqThreads), 0, s, u, p.u_t, p.u_pair,
+                     p.n_specs, p.fam_off[KS_NFAM], p.o_troof, p.o_eta, p.o_t, total, slots, per);
+  return hipGetLastError();
 }
 
 hipError_t launch_unique(const UniqParams &p, hipStream_t s) {

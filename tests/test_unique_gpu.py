@@ -1,15 +1,16 @@
-"""Step sums over the different records of a call (GPU): calls with enough
-head work evaluate equal records once and weight them.  The reference is the
-same call with per-pair outputs, which evaluates every record: its t_kernel
-summed in float64 per step.  Both paths form the same fp32 t for a record, and
-the weights (counts times multiplicities below 2^24) are exact in fp32, so only
-the order of the float64 sums differs: with at most 4096 non-negative terms a
-step, 4096 2^-53 < 1e-12 relative."""
+"""The different records of a call (GPU): calls with enough head work evaluate
+equal records once, weight them in the step sums and spread their per-pair
+values.  The reference is the same call in a workspace with no room for that,
+which evaluates every record.  Both form the same fp32 values for a record, so
+per-pair outputs are equal bit for bit; the step sums are compared with the
+float64 sum of the reference's t_kernel: the weights (counts times
+multiplicities below 2^24) are exact in fp32, so only the order of the float64
+sums differs, and with at most 4096 non-negative terms a step that is within
+4096 2^-53 < 1e-12."""
 import numpy as np
 import pytest
 
 from paper_2606_28565_amd import abi
-from tests import gpu_helpers as g
 from tests.helpers import make_desc, steprec
 from workload import gen
 
@@ -25,16 +26,57 @@ def _wl(rows, reqs, heads, n_specs, mult=None, expert_rows=()):
                         gen.specs_grid(n_specs, 77), heads, gen.HostConsts())
 
 
+def _every_record_bytes(wl):
+    """The workspace of a call that evaluates every record."""
+    up = lambda x: -(-x // 256) * 256
+    S, N = wl.desc.n_steps, wl.n_specs
+    tiles = sum(-(-int(k) // 64) for k in np.diff(wl.desc.fam_off))
+    return 256 + up(64 * N) + up(32 * S) + up(80 * S) + up(80 * N * S) + up(8 * N * tiles)
+
+
+def _run(wl, room, outs=False, steps=True, grid=None):
+    """outs: every per-pair output and the counts (False: none; "pairs": no
+    counts).  room: whether the different records have room."""
+    import torch
+    di = abi.DeviceInputs(wl)
+    small = _every_record_bytes(wl)
+    assert small < di.ws_bytes
+    wsb = di.ws_bytes if room else small
+    heads = di.make_heads(wl.heads.precision, wl.heads.in_dim, wl.heads.hidden, abi.KS_ETA_MLP, None, grid)
+    so_t, so = abi.step_outputs(wl.desc.n_steps, di.n_specs)
+    ko_t, ko = abi.kernel_outputs(wl.desc.n_rows, di.n_specs, counts=outs is True) if outs else ({}, None)
+    for t in list(so_t.values()) + list(ko_t.values()):
+        t.fill_(-1)
+    if steps:
+        abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, di.n_specs, heads, di.host, so, ko, di.ws_ptr, wsb,
+                          abi.current_stream())
+    else:
+        abi.ks_eval_kernels(di.desc, di.specs_ptr, di.n_specs, heads, ko, di.ws_ptr, wsb, abi.current_stream())
+    torch.cuda.synchronize()
+    status = abi.ks_device_status(di.ws_ptr, wsb, abi.current_stream(), check=False)
+    got = {k: v.cpu().numpy() for k, v in (list(so_t.items()) if steps else []) + list(ko_t.items())}
+    return got, status
+
+
 def _check(wl, grid=None, tol=TOL):
-    pairs = g.eval_steps(wl, counts=False, grid=grid)
-    sums = g.eval_steps(wl, per_pair=False, grid=grid)
+    ref, _ = _run(wl, False, "pairs", grid=grid)
+    sums, st = _run(wl, True, grid=grid)
+    assert st == abi.KS_OK
     d = wl.desc
     w = np.ones(d.n_rows) if getattr(d, "mult", None) is None else d.mult.astype(np.float64)
     for s in range(wl.n_specs):
-        body = np.bincount(d.step, weights=pairs["t_kernel"][s].astype(np.float64) * w, minlength=d.n_steps)
+        body = np.bincount(d.step, weights=ref["t_kernel"][s].astype(np.float64) * w, minlength=d.n_steps)
         np.testing.assert_allclose(sums["t_body"][s], body, rtol=tol)
     for k in ("t_gpu", "t_step"):   # the other path's sums are fp32 within 64-record tiles
-        np.testing.assert_allclose(sums[k], pairs[k], rtol=1e-6)
+        np.testing.assert_allclose(sums[k], ref[k], rtol=1e-6)
+    for outs, steps in (("pairs", True), (True, False)):
+        every, _ = _run(wl, False, outs, steps, grid)
+        got, _ = _run(wl, True, outs, steps, grid)
+        for k in every:
+            if k.startswith("t_") and k not in ("t_roof", "t_kernel"):
+                np.testing.assert_allclose(got[k], sums[k], rtol=tol)
+            else:
+                np.testing.assert_array_equal(got[k], every[k], err_msg=k)
 
 
 def _reqs(rng, n):
@@ -64,7 +106,7 @@ def test_layers_repeat(kernels, layers):
         for f in fams:
             if rng.random() < 0.9:
                 rows += _family(rng, f, j, kernels, layers if rng.random() < 0.8 else layers + 1)
-    wl = _wl(rows, _reqs(rng, n_steps), gen.make_heads(16, 128, "bf16"), 160)
+    wl = _wl(rows, _reqs(rng, n_steps), gen.make_heads(16, 128, "bf16"), 180)
     _check(wl, tol=6 * 2.0 ** -24 if kernels == 5 and layers > 1 else TOL)
 
 
@@ -76,12 +118,12 @@ def test_one_long_step_and_chunk_edges(run):
     rows = [(gen.ROPE, 0, 17, 8, 128, 0, 0)]
     rows += [(gen.ROPE, 1, 33, 8, 128, 0, 0)] * run
     rows += [(gen.ROPE, 2 + i, int(rng.integers(1, 64)), 8, 128, 0, 0) for i in range(2100)]
-    wl = _wl(rows, _reqs(rng, 2102), gen.make_heads(32, 64, "f32"), 64)
+    wl = _wl(rows, _reqs(rng, 2102), gen.make_heads(32, 64, "f32"), 256)
     _check(wl)
 
 
-@pytest.mark.parametrize("precision,in_dim,hidden,n_specs", [("f32", 16, 64, 64), ("bf16", 32, 256, 64),
-                                                             ("bf16", 16, 64, 400)])
+@pytest.mark.parametrize("precision,in_dim,hidden,n_specs", [("f32", 16, 64, 80), ("bf16", 32, 256, 64),
+                                                             ("bf16", 16, 64, 680)])
 def test_multiplicities_and_shared_slots(precision, in_dim, hidden, n_specs):
     """Multiplicities (equal records with different ones stay apart), and token
     counts a table's size apart, which meet in one slot."""
@@ -104,10 +146,13 @@ def test_records_that_do_not_repeat_fall_back():
     for j in range(24):
         rows += [(gen.GEMM, j, 1 + i + 200 * j, 512, 256, 0, 0) for i in range(200)]
         rows += [(gen.RMSNORM, j, 5 + j, 4096, 0, 0, 0)] * 64
-    wl = _wl(rows, _reqs(rng, 24), gen.make_heads(16, 128, "bf16"), 160)
-    pairs, sums = g.eval_steps(wl, counts=False), g.eval_steps(wl, per_pair=False)
-    for k in ("t_body", "t_gpu", "t_step"):   # both evaluate every record, alike
-        np.testing.assert_array_equal(sums[k], pairs[k])
+    wl = _wl(rows, _reqs(rng, 24), gen.make_heads(16, 128, "bf16"), 220)
+    for outs in (False, "pairs", True):
+        ref, _ = _run(wl, False, outs)
+        got, st = _run(wl, True, outs)
+        assert st == abi.KS_OK
+        for k in ref:   # both evaluate every record, alike
+            np.testing.assert_array_equal(got[k], ref[k], err_msg=k)
 
 
 @pytest.mark.parametrize("grids", [False, True])
@@ -123,56 +168,38 @@ def test_grouped_gemms_and_grids(grids):
                      (gen.GROUPED_GEMM, j, 0, 4096, 14336, 8, len(experts))]
             experts += [int(x) for x in rng.integers(0, 300, 8)]
         rows += _family(rng, gen.GEMM, j, 3, 16) + _family(rng, gen.SILU_MUL, j, 1, 16)
-    wl = _wl(rows, _reqs(rng, 40), gen.make_heads(16, 128, "bf16"), 200, expert_rows=experts)
+    wl = _wl(rows, _reqs(rng, 40), gen.make_heads(16, 128, "bf16"), 345, expert_rows=experts)
     _check(wl, grid=gen.make_grid(gen.GRID_ALL) if grids else None, tol=6 * 2.0 ** -24)
 
 
 def test_bad_steps_are_skipped_and_reported():
-    """Records whose step is out of range are left out and flagged."""
-    import torch
+    """Records whose step is out of range are left out of the sums and flagged;
+    with per-pair outputs every record is evaluated, those too."""
     rng = np.random.Generator(np.random.PCG64(8))
     rows = [(gen.ROPE, j, 1 + j % 50, 8, 128, 0, 0) for j in range(4000)]
-    good = _wl(rows, _reqs(rng, 4000), gen.make_heads(16, 128, "bf16"), 200)
+    good = _wl(rows, _reqs(rng, 4000), gen.make_heads(16, 128, "bf16"), 250)
     bad = _wl(rows + [(gen.ROPE, 4000 + i, 3, 8, 128, 0, 0) for i in range(1500)], [[(1, 1)]] * 4000,
-              gen.make_heads(16, 128, "bf16"), 200)
+              gen.make_heads(16, 128, "bf16"), 250)
     bad.desc.req_off, bad.desc.req_q, bad.desc.req_h = good.desc.req_off, good.desc.req_q, good.desc.req_h
-    ref = g.eval_steps(good, per_pair=False)
-    di = abi.DeviceInputs(bad)
-    so_t, so = abi.step_outputs(bad.desc.n_steps, di.n_specs)
-    abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, di.n_specs, di.heads, di.host, so, None, di.ws_ptr,
-                      di.ws_bytes, abi.current_stream())
-    torch.cuda.synchronize()
-    st = abi.ks_device_status(di.ws_ptr, di.ws_bytes, abi.current_stream(), check=False)
-    assert st == abi.KS_EINVAL
-    for k in ("t_body", "t_gpu", "t_step"):
-        np.testing.assert_allclose(so_t[k].cpu().numpy(), ref[k], rtol=TOL)
+    ref, _ = _run(good, True)
+    for outs, tol in ((False, TOL), ("pairs", 6 * 2.0 ** -24), (True, 6 * 2.0 ** -24)):
+        got, st = _run(bad, True, outs)
+        assert st == abi.KS_EINVAL
+        for k in ("t_body", "t_gpu", "t_step"):
+            np.testing.assert_allclose(got[k], ref[k], rtol=tol)
+        if outs:
+            every, _ = _run(bad, False, outs)
+            for k in every:
+                np.testing.assert_array_equal(got[k], every[k], err_msg=k)
 
 
 @pytest.mark.parametrize("n_specs", [1, 2, 3, 4, 5, 16, 33])
-def test_workspace_without_room_evaluates_every_record(n_specs):
-    """The step sums' kernels by spec count, and the same call in a workspace
-    with no room for the different records (as large as the part both forms
-    use): equal within the fp32 tile sums of the latter."""
-    import torch
+def test_step_sums_by_spec_count(n_specs):
+    """The step sums' kernels: up to four specs, more, a tile's remainder."""
     rng = np.random.Generator(np.random.PCG64(9))
     rows = []
     n_steps = 6000 // n_specs + 50
     for j in range(n_steps):
         rows += _family(rng, gen.GEMM, j, 4, 20) + [(gen.ATTN_DECODE, j, 0, 32, 128, 8, 0)] * 20
         rows += [(gen.LM_HEAD, j, 1 + j % 64, 32000, 4096, 0, 0)]
-    wl = _wl(rows, _reqs(rng, n_steps), gen.make_heads(32, 128, "f32"), n_specs)
-    _check(wl)
-    di = abi.DeviceInputs(wl)
-    outs = []
-    tiles = sum(-(-int(k) // 64) for k in np.diff(wl.desc.fam_off))
-    small = 256 + 256 * (-(-64 * n_specs // 256)) + 256 * 4 + 32 * n_steps + 80 * n_steps \
-        + 80 * n_specs * n_steps + 8 * n_specs * tiles + 256
-    assert small < di.ws_bytes
-    for wsb in (di.ws_bytes, small):
-        so_t, so = abi.step_outputs(n_steps, n_specs)
-        abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, n_specs, di.heads, di.host, so, None, di.ws_ptr, wsb,
-                          abi.current_stream())
-        torch.cuda.synchronize()
-        outs.append({k: v.cpu().numpy() for k, v in so_t.items()})
-    for k in outs[0]:
-        np.testing.assert_allclose(outs[0][k], outs[1][k], rtol=1e-6)
+    _check(_wl(rows, _reqs(rng, n_steps), gen.make_heads(32, 128, "f32"), n_specs))
