@@ -51,9 +51,9 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 //             per-step arrays (u32 [S] each), R = records of one step
 //   expand  : ks_expand's workspace for S steps
 //   eval    : ks_eval_steps' workspace for S steps and S specs
-//   outputs : t_body, t_gpu, t_step (f64 [S][S]), each step's own latency (f64 [S])
+//   outputs : t_body, t_gpu, t_step (f64 [S][S])
 struct SimLayout {
-  size_t stage, rec, expand, eval, outs, lat, total;
+  size_t stage, rec, expand, eval, outs, total;
   size_t expand_bytes, eval_bytes;
   int64_t R, S, Q;
 };
@@ -87,8 +87,6 @@ bool sim_layout(const ks_model *md, const ks_sched *sc, int32_t n_sims, SimLayou
   off += align256(L->eval_bytes);
   L->outs = off;
   off += align256(3 * S * S * sizeof(double));
-  L->lat = off;
-  off += align256(S * sizeof(double));
   L->total = off;
   return true;
 }
@@ -382,7 +380,6 @@ ks_status ks_simulate(const ks_model *model, const ks_spec *specs, int32_t n_spe
   rec.tp = rec.layers + 2 * S;
   rec.n_launch = rec.layers + 3 * S;
   double *d_out = reinterpret_cast<double *>(w + L.outs);
-  double *d_lat = reinterpret_cast<double *>(w + L.lat);
 
   std::vector<Sim> sims;
   sims.reserve((size_t)S);
@@ -395,10 +392,11 @@ ks_status ks_simulate(const ks_model *model, const ks_spec *specs, int32_t n_spe
   std::vector<int64_t> who;             // the simulation of each step of the round
   std::vector<uint32_t> h_off, h_q, h_h, h_spec;
   std::vector<uint8_t> h_pre;
-  // the round's packed batch and its latencies cross PCIe through pinned
-  // host buffers (asynchronous DMA rather than a staged pageable copy),
-  // sized like the workspace's stage region; each round's synchronization
-  // ends its copies before the buffers are reused
+  // the round's packed batch crosses PCIe from a pinned host buffer
+  // (asynchronous DMA rather than a staged pageable copy), sized like the
+  // workspace's stage region, and its latencies are written to another by the
+  // last kernel; each round's synchronization ends both before the buffers are
+  // reused
   struct Pinned {
     void *p = nullptr;
     ~Pinned() {
@@ -497,11 +495,10 @@ ks_status ks_simulate(const ks_model *model, const ks_spec *specs, int32_t n_spe
     // every step against every spec (all pairs); each simulation keeps its own
     // (and each step's latency under its own simulation's spec, in the same
     // launches)
-    st = ks::eval_steps_own(&d, &stp, specs, n_specs, heads, host, &so, w + L.eval, L.eval_bytes, d_own, d_lat,
-                            stream);
+    // straight to the pinned buffer (a copy of its own took as long as a kernel)
+    st = ks::eval_steps_own(&d, &stp, specs, n_specs, heads, host, &so, w + L.eval, L.eval_bytes, d_own, lat, stream);
     if (st != KS_OK) return st;
-    e = hipMemcpyAsync(lat, d_lat, A * sizeof(double), hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return ks::set_error(KS_EHIP, "step latency readback: %s", hipGetErrorString(e));
     for (int64_t i = 0; i < A; ++i) {
       const int64_t s = who[(size_t)i];
