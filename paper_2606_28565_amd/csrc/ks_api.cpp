@@ -135,7 +135,7 @@ bool uniq_plan(const ks_desc *d, int32_t n_specs, UniqPlan *pl) {
     pl->unit_off[f] = (int32_t)units;
     slots += ns;
     scans += (ns + ks::kUniqScan - 1) / ks::kUniqScan;
-    units += flat ? 4 * n : n;
+    units += flat ? 4 * n : (n + 3) / 4;
     if (slots >= (int64_t(1) << 30)) return false;
     chunks += n;
     ent += n * pl->chunk_entries[f];
@@ -363,8 +363,9 @@ void fill_eval(ks::EvalParams &p, const ks_desc *d, const ks_spec *specs, int32_
 }
 
 // Whether a call evaluates only its different records: MLP heads, given the
-// workspace for it, and enough head work; twice as much with per-pair outputs,
-// which one or two more kernels spread.  (Their sources come with the direct
+// workspace for it, and enough head work; three times as much with per-pair
+// outputs, which one or two more kernels spread (a 7B trace of 2.1 times the line
+// takes 54 us spread and 50 us directly).  (Their sources come with the direct
 // evaluation of a grid.)
 bool takes_uniq(const ks_desc *d, int32_t n_specs, const ks_heads *h, int kind, const ks_kernel_out *kout,
                 size_t ws_bytes, UniqPlan *pl, Layout *L, bool *pair) {
@@ -373,7 +374,7 @@ bool takes_uniq(const ks_desc *d, int32_t n_specs, const ks_heads *h, int kind, 
   const bool out = kout && (*pair || kout->flops || kout->bytes || kout->blocks);
   if (kout && kout->source && h->grid_mask) return false;
   const double flops = 2.0 * (double)d->n_rows * n_specs * h->hidden * (h->in_dim + h->hidden);
-  if (flops < (out ? 2.0 : 1.0) * (h->precision == KS_F32 ? kUniqF32Flops : kUniqBf16Flops)) return false;
+  if (flops < (out ? 3.0 : 1.0) * (h->precision == KS_F32 ? kUniqF32Flops : kUniqBf16Flops)) return false;
   if (!uniq_plan(d, n_specs, pl)) return false;
   const Layout full = layout_of(d, n_specs, pl);
   if (ws_bytes < (*pair ? full.total : full.sums)) return false;

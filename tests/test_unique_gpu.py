@@ -106,7 +106,7 @@ def test_layers_repeat(kernels, layers):
         for f in fams:
             if rng.random() < 0.9:
                 rows += _family(rng, f, j, kernels, layers if rng.random() < 0.8 else layers + 1)
-    wl = _wl(rows, _reqs(rng, n_steps), gen.make_heads(16, 128, "bf16"), 180)
+    wl = _wl(rows, _reqs(rng, n_steps), gen.make_heads(16, 128, "bf16"), 270)
     _check(wl, tol=6 * 2.0 ** -24 if kernels == 5 and layers > 1 else TOL)
 
 
@@ -118,12 +118,12 @@ def test_one_long_step_and_chunk_edges(run):
     rows = [(gen.ROPE, 0, 17, 8, 128, 0, 0)]
     rows += [(gen.ROPE, 1, 33, 8, 128, 0, 0)] * run
     rows += [(gen.ROPE, 2 + i, int(rng.integers(1, 64)), 8, 128, 0, 0) for i in range(2100)]
-    wl = _wl(rows, _reqs(rng, 2102), gen.make_heads(32, 64, "f32"), 256)
+    wl = _wl(rows, _reqs(rng, 2102), gen.make_heads(32, 64, "f32"), 370)
     _check(wl)
 
 
-@pytest.mark.parametrize("precision,in_dim,hidden,n_specs", [("f32", 16, 64, 80), ("bf16", 32, 256, 64),
-                                                             ("bf16", 16, 64, 680)])
+@pytest.mark.parametrize("precision,in_dim,hidden,n_specs", [("f32", 16, 64, 120), ("bf16", 32, 256, 72),
+                                                             ("bf16", 16, 64, 1000)])
 def test_multiplicities_and_shared_slots(precision, in_dim, hidden, n_specs):
     """Multiplicities (equal records with different ones stay apart), and token
     counts a table's size apart, which meet in one slot."""
@@ -146,7 +146,7 @@ def test_records_that_do_not_repeat_fall_back():
     for j in range(24):
         rows += [(gen.GEMM, j, 1 + i + 200 * j, 512, 256, 0, 0) for i in range(200)]
         rows += [(gen.RMSNORM, j, 5 + j, 4096, 0, 0, 0)] * 64
-    wl = _wl(rows, _reqs(rng, 24), gen.make_heads(16, 128, "bf16"), 220)
+    wl = _wl(rows, _reqs(rng, 24), gen.make_heads(16, 128, "bf16"), 320)
     for outs in (False, "pairs", True):
         ref, _ = _run(wl, False, outs)
         got, st = _run(wl, True, outs)
@@ -168,7 +168,7 @@ def test_grouped_gemms_and_grids(grids):
                      (gen.GROUPED_GEMM, j, 0, 4096, 14336, 8, len(experts))]
             experts += [int(x) for x in rng.integers(0, 300, 8)]
         rows += _family(rng, gen.GEMM, j, 3, 16) + _family(rng, gen.SILU_MUL, j, 1, 16)
-    wl = _wl(rows, _reqs(rng, 40), gen.make_heads(16, 128, "bf16"), 345, expert_rows=experts)
+    wl = _wl(rows, _reqs(rng, 40), gen.make_heads(16, 128, "bf16"), 520, expert_rows=experts)
     _check(wl, grid=gen.make_grid(gen.GRID_ALL) if grids else None, tol=6 * 2.0 ** -24)
 
 
@@ -177,9 +177,9 @@ def test_bad_steps_are_skipped_and_reported():
     with per-pair outputs every record is evaluated, those too."""
     rng = np.random.Generator(np.random.PCG64(8))
     rows = [(gen.ROPE, j, 1 + j % 50, 8, 128, 0, 0) for j in range(4000)]
-    good = _wl(rows, _reqs(rng, 4000), gen.make_heads(16, 128, "bf16"), 250)
+    good = _wl(rows, _reqs(rng, 4000), gen.make_heads(16, 128, "bf16"), 360)
     bad = _wl(rows + [(gen.ROPE, 4000 + i, 3, 8, 128, 0, 0) for i in range(1500)], [[(1, 1)]] * 4000,
-              gen.make_heads(16, 128, "bf16"), 250)
+              gen.make_heads(16, 128, "bf16"), 360)
     bad.desc.req_off, bad.desc.req_q, bad.desc.req_h = good.desc.req_off, good.desc.req_q, good.desc.req_h
     ref, _ = _run(good, True)
     for outs, tol in ((False, TOL), ("pairs", 6 * 2.0 ** -24), (True, 6 * 2.0 ** -24)):
