@@ -74,8 +74,12 @@ def kernel_source_hash() -> str:
     import hashlib
     import re
     h = hashlib.sha256()
-    for f in ("ks_kernels.hip", "ks_expand.hip", "ks_internal.h", "ks_sched.inc"):
-        with open(os.path.join(ROOT, "paper_2606_28565_amd", "csrc", f)) as fh:
+    src = os.path.join(ROOT, "paper_2606_28565_amd", "csrc")
+    for f in ("ks_kernels.hip", "ks_expand.hip", "ks_internal.h", "ks_sched.inc", "ks_unique.hip", "ks_finish.hip",
+              "ks_agg.h"):
+        if not os.path.exists(os.path.join(src, f)):
+            continue
+        with open(os.path.join(src, f)) as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
         text = re.sub(r"//[^\n]*", "", text)
@@ -157,6 +161,27 @@ def stream_bytes(wl, n_specs: int, sums: bool = True, pair_outputs: int = 0) -> 
 def head_flops_per_pair(in_dim: int, hidden: int) -> int:
     """Algorithmic MLP FLOPs of one prediction: 2 (in h + h h + h)."""
     return 2 * (in_dim * hidden + hidden * hidden + hidden)
+
+
+def different_records(t: dict, fam_off) -> int:
+    """How many records of a call differ in the fields their latency depends
+    on: the head evaluates each of them once for every spec vector, and the
+    call's predictions, one per record and spec vector, come from those.
+    Dense records by (m, n, k), attention by (step, n, k, a); grouped GEMMs
+    all (each has its own routed rows).  t: the record fields on the GPU."""
+    import torch
+    total = 0
+    for f in range(len(fam_off) - 1):
+        lo, hi = int(fam_off[f]), int(fam_off[f + 1])
+        if f == 2 or hi - lo < 2:
+            total += hi - lo
+            continue
+        x = {name: t[name][lo:hi].long() for name in ("step", "m", "n", "k", "a")}
+        k = 0 if f in (5, 7, 9) else x["k"]      # RMSNorm, SiLU and embedding have no K
+        key = ((x["step"] << 36) | (x["n"] << 24) | (k << 12) | x["a"]) if f in (3, 4) else \
+            ((x["m"] << 36) | (x["n"] << 18) | k)
+        total += int(torch.unique(key).numel())
+    return total
 
 
 def host_threads() -> int:
@@ -528,6 +553,7 @@ def _bench_sweep(args) -> int:
         bound, unit, peak, dtype = "hbm", "GB/s", PEAK["hbm"] / 1e9, "f32"
         achieved = alg / (k_ms * 1e-3) / 1e9
     else:
+        eval_rows = sum(different_records((pt["db"] or pt["di"]).t, pt["desc"].fam_off) for pt in parts)
         alg = float(eval_rows) * n_specs * head_flops_per_pair(in_dim, hidden)
         bound, unit, peak, dtype = "mfma", "TFLOP/s", PEAK["bf16"] / 1e12, "bf16"
         achieved = alg / (k_ms * 1e-3) / 1e12
@@ -544,8 +570,8 @@ def _bench_sweep(args) -> int:
         "step_evals_per_s": n_steps_total * n_specs / (ms * 1e-3),
         "roofline": {"bound": bound, "achieved": achieved, "peak": peak, "unit": unit, "frac": achieved / peak,
                      "traffic": recorded_traffic(traffic_key(args)), "kernel_ms": k_ms,
-                     "note": "achieved = algorithmic work of the sweep's evaluation-kernel launches (head "
-                             "FLOPs over the records evaluated, or the bytes the model reads and writes) / "
+                     "note": "achieved = algorithmic work of the sweep's evaluations (head FLOPs over the "
+                             "different records, or the bytes the model reads and writes) / "
                              "the sum of those kernels' mean durations from HIP events around each launch; "
                              "traffic = HBM bytes of those launches per sweep (counters)"},
         "calls": [{"name": pt["name"], "records": pt["rows"], "kernel_ms": pt["kernel_ms"],
@@ -843,8 +869,13 @@ def main() -> int:
         achieved = alg / (k_ms * 1e-3) / 1e9 if alg is not None else None
         dtype = "f32"
     else:
+        # the head's work is per different record; of those in the share of the
+        # pairs that are left to it (bounded families and grids take the others)
         per_pair = head_flops_per_pair(wl.heads.in_dim, wl.heads.hidden)
-        alg = float(mlp_pairs) * per_pair
+        src = (db.t, db.fam_off) if db is not None else (di.t, wl.desc.fam_off)
+        different = different_records(*src)
+        alg = float(mlp_pairs) / n_eval * different * per_pair
+        n_eval = different
         bf16 = wl.heads.precision == "bf16"
         bound, unit = "mfma", "TFLOP/s"
         peak = (PEAK["bf16"] if bf16 else PEAK["f32"]) / 1e12
@@ -872,10 +903,11 @@ def main() -> int:
                      "frac": achieved / peak if achieved is not None else None,
                      "traffic": recorded_traffic(traffic_key(args)),
                      "kernel_ms": k_ms, "evaluated_records": n_eval,
-                     "note": "achieved = algorithmic work of one evaluation-kernel launch (FLOPs of the "
-                             "head over the records it evaluates, or the bytes the model reads and "
-                             "writes) / that kernel's mean duration from HIP events recorded around "
-                             "its launch on the call's stream"},
+                     "note": "achieved = algorithmic work of one evaluation (FLOPs of the head over the "
+                             "different records, each evaluated once per spec vector, or the bytes the "
+                             "model reads and writes) / the mean duration of its kernels (finding the "
+                             "different records among them) from HIP events around them on the call's "
+                             "stream"},
     }
     if exp is not None:
         out["expand"] = exp

@@ -203,3 +203,62 @@ def test_step_sums_by_spec_count(n_specs):
         rows += _family(rng, gen.GEMM, j, 4, 20) + [(gen.ATTN_DECODE, j, 0, 32, 128, 8, 0)] * 20
         rows += [(gen.LM_HEAD, j, 1 + j % 64, 32000, 4096, 0, 0)]
     _check(_wl(rows, _reqs(rng, n_steps), gen.make_heads(32, 128, "f32"), n_specs))
+
+
+def _trace_wl(n_steps, n_specs):
+    rng = np.random.Generator(np.random.PCG64(10))
+    rows = []
+    for j in range(n_steps):
+        rows += _family(rng, gen.GEMM, j, 4, 16) + [(gen.ATTN_DECODE, j, 0, 32, 128, 8, 0)] * 16
+        rows += [(gen.RMSNORM, j, 1 + j % 40, 4096, 0, 0, 0)] * 32
+    return _wl(rows, _reqs(rng, n_steps), gen.make_heads(16, 128, "bf16"), n_specs)
+
+
+def test_static_entry_at_its_limit():
+    """A call whose workspace fits the fixed array only without the different
+    records' part is accepted, and evaluates every record."""
+    import torch
+    wl = _trace_wl(600, 700)
+    di = abi.DeviceInputs(wl)
+    assert _every_record_bytes(wl) <= abi.KS_STATIC_SCRATCH_BYTES < di.ws_bytes
+    so_t, so = abi.step_outputs(600, 700)
+    flags = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    abi.ks_eval_steps_static(di.desc, di.steps, di.specs_ptr, di.n_specs, di.heads, di.host, so, None,
+                             flags.data_ptr(), abi.current_stream())
+    torch.cuda.synchronize()
+    ref, _ = _run(wl, False)
+    assert int(flags.item()) == 0
+    for k in ref:
+        np.testing.assert_array_equal(so_t[k].cpu().numpy(), ref[k], err_msg=k)
+
+
+def test_graph_replays():
+    """Captured into a graph and replayed on changed inputs, with eager calls in
+    the same workspace between the replays: every replay equals the eager call."""
+    import torch
+    wl = _trace_wl(300, 300)
+    di = abi.DeviceInputs(wl)
+    so_t, so = abi.step_outputs(300, 300)
+    eo_t, eo = abi.step_outputs(300, 300)
+
+    def call(out):
+        abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, di.n_specs, di.heads, di.host, out, None, di.ws_ptr,
+                          di.ws_bytes, abi.current_stream())
+
+    call(so)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(so)
+    m = di.t["m"].clone()
+    for i in range(4):
+        di.t["m"].copy_(m + 37 * i * (torch.arange(len(m), device=m.device) // 64 % 3 == 0))
+        for t in so_t.values():
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = {k: v.clone() for k, v in so_t.items()}
+        call(eo)
+        torch.cuda.synchronize()
+        for k in got:
+            assert torch.equal(got[k], eo_t[k]), (i, k)
