@@ -370,7 +370,7 @@ size_t ks_simulate_workspace_bytes(const ks_model* model, const ks_sched* sched,
 
 /* Runs n_specs simulations (1 .. 256) to completion (synchronous: it waits
  * for each round's latencies on `stream`).  The one entry point that
- * allocates: two pinned HOST buffers for the rounds' copies (the round's
+ * allocates: two pinned HOST buffers for the rounds' transfers (the round's
  * packed batch, 8 max_num_seqs + 9 bytes per simulation plus 4, and its
  * latencies, 8 bytes per simulation), freed before it returns.  specs:
  * DEVICE array of n_specs
@@ -391,7 +391,8 @@ ks_status ks_simulate(const ks_model* model, const ks_spec* specs, int32_t n_spe
  * need for this record set and spec count (256-byte aligned).  0 on bad
  * arguments.  For large record sets this includes room for their different
  * records (kernels that recur from layer to layer or step to step with equal
- * fields), which step sums of MLP heads evaluate once each. */
+ * fields), which MLP heads evaluate once each; in a smaller workspace that
+ * still holds the rest (as large as without them) every record is evaluated. */
 size_t ks_workspace_bytes(const ks_desc* desc, int32_t n_specs);
 
 /* Per-pair latencies (Eq. 2) for every spec vector and record.  ws: device
@@ -415,8 +416,9 @@ ks_status ks_eval_steps(const ks_desc* desc, const ks_steps* steps,
  * forbid hipMalloc.  Same arguments, checks and results as ks_eval_steps,
  * without the workspace: the library uses a fixed device array of
  * KS_STATIC_SCRATCH_BYTES on each GPU instead (held from the library's load
- * on that GPU until the process ends).  A call whose ks_workspace_bytes()
- * exceeds it fails with KS_ERANGE before any launch.  Every call on one GPU
+ * on that GPU until the process ends).  A call that needs more than it to
+ * evaluate every record fails with KS_ERANGE before any launch; one that has
+ * no room for the different records besides evaluates every record.  Every call on one GPU
  * shares that GPU's array and leaves its contents behind: calls that
  * overlap on one GPU (other streams, other threads) race.  flags: a device
  * uint32 or NULL; if set, the call's bad-data flag word is copied there on

@@ -16,6 +16,10 @@
 //                no measured grid (eta = 1, the bounded head): the same per
 //                256 records and wave, four consecutive records per lane
 //   k_finish     per (spec, step): body sum, all-reduce (Eq. 3), assembly (Eq. 4)
+// k_prologue is the first two for a call of few steps.  Calls with an MLP head
+// and enough head work find their different records first (k_unique, k_join)
+// and evaluate those (k_eval's kVarUniq); their sums are k_finish_few's or
+// k_finish_list's, their per-pair outputs k_spread's and k_counts'.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
