@@ -448,9 +448,11 @@ ks_status ks_device_status(const void* ws, size_t ws_bytes, hipStream_t stream);
 
 /* Measurement hook for benchmarks: with both events non-NULL, every later
  * call on this thread of ks_eval_kernels / ks_eval_steps records `before` on
- * its stream right before the evaluation kernel and `after` right after it,
- * and every ks_expand call does the same around its record-writing kernel,
- * so hipEventElapsedTime(before, after) is that one kernel's duration.
+ * its stream right before the evaluation and `after` right after it (one
+ * kernel, or, where the different records are evaluated, the kernels that
+ * find them, evaluate them and spread their per-pair outputs), and every
+ * ks_expand call does the same around its record-writing kernel, so
+ * hipEventElapsedTime(before, after) is their duration.
  * Calling it with NULLs turns the hook off.  The events are the caller's
  * (created with timing enabled, never destroyed by the library). */
 ks_status ks_set_timing_events(hipEvent_t before, hipEvent_t after);

@@ -34,7 +34,7 @@ def _every_record_bytes(wl):
     return 256 + up(64 * N) + up(32 * S) + up(80 * S) + up(80 * N * S) + up(8 * N * tiles)
 
 
-def _run(wl, room, outs=False, steps=True, grid=None):
+def _run(wl, room, outs=False, steps=True, grid=None, bounded=None):
     """outs: every per-pair output and the counts (False: none; "pairs": no
     counts).  room: whether the different records have room."""
     import torch
@@ -42,7 +42,7 @@ def _run(wl, room, outs=False, steps=True, grid=None):
     small = _every_record_bytes(wl)
     assert small < di.ws_bytes
     wsb = di.ws_bytes if room else small
-    heads = di.make_heads(wl.heads.precision, wl.heads.in_dim, wl.heads.hidden, abi.KS_ETA_MLP, None, grid)
+    heads = di.make_heads(wl.heads.precision, wl.heads.in_dim, wl.heads.hidden, abi.KS_ETA_MLP, bounded, grid)
     so_t, so = abi.step_outputs(wl.desc.n_steps, di.n_specs)
     ko_t, ko = abi.kernel_outputs(wl.desc.n_rows, di.n_specs, counts=outs is True) if outs else ({}, None)
     for t in list(so_t.values()) + list(ko_t.values()):
@@ -58,9 +58,9 @@ def _run(wl, room, outs=False, steps=True, grid=None):
     return got, status
 
 
-def _check(wl, grid=None, tol=TOL):
-    ref, _ = _run(wl, False, "pairs", grid=grid)
-    sums, st = _run(wl, True, grid=grid)
+def _check(wl, grid=None, tol=TOL, bounded=None):
+    ref, _ = _run(wl, False, "pairs", grid=grid, bounded=bounded)
+    sums, st = _run(wl, True, grid=grid, bounded=bounded)
     assert st == abi.KS_OK
     d = wl.desc
     w = np.ones(d.n_rows) if getattr(d, "mult", None) is None else d.mult.astype(np.float64)
@@ -70,8 +70,8 @@ def _check(wl, grid=None, tol=TOL):
     for k in ("t_gpu", "t_step"):   # the other path's sums are fp32 within 64-record tiles
         np.testing.assert_allclose(sums[k], ref[k], rtol=1e-6)
     for outs, steps in (("pairs", True), (True, False)):
-        every, _ = _run(wl, False, outs, steps, grid)
-        got, _ = _run(wl, True, outs, steps, grid)
+        every, _ = _run(wl, False, outs, steps, grid, bounded)
+        got, _ = _run(wl, True, outs, steps, grid, bounded)
         for k in every:
             if k.startswith("t_") and k not in ("t_roof", "t_kernel"):
                 np.testing.assert_allclose(got[k], sums[k], rtol=tol)
@@ -212,6 +212,23 @@ def _trace_wl(n_steps, n_specs):
         rows += _family(rng, gen.GEMM, j, 4, 16) + [(gen.ATTN_DECODE, j, 0, 32, 128, 8, 0)] * 16
         rows += [(gen.RMSNORM, j, 1 + j % 40, 4096, 0, 0, 0)] * 32
     return _wl(rows, _reqs(rng, n_steps), gen.make_heads(16, 128, "bf16"), n_specs)
+
+
+@pytest.mark.parametrize("bounded", [False, True])
+@pytest.mark.parametrize("kind", ["dense", "moe"])
+def test_whole_traces(kind, bounded):
+    """Every family (KV writes among them), prefill and decode steps; with some
+    families on the bounded head.  The mixture of experts' grouped GEMMs are
+    summed in fp32 within 64-record tiles (6 2^-24)."""
+    import dataclasses
+    shape = dataclasses.replace(gen.MIXTRAL if kind == "moe" else gen.LLAMA7B, kv_write=True)
+    tr = gen.trace_uniform(shape, 60, 11)
+    if kind == "moe":
+        tr.experts = gen.route_tokens(tr, 12)
+    desc, rec = gen.build([tr])
+    wl = gen.Workload("trace", desc, rec, gen.specs_grid(130, 78), gen.make_heads(16, 128, "bf16"), gen.HostConsts())
+    _check(wl, tol=6 * 2.0 ** -24 if kind == "moe" else TOL,
+           bounded=gen.make_bounded(gen.BOUNDED_MIXED) if bounded else None)
 
 
 def test_static_entry_at_its_limit():
