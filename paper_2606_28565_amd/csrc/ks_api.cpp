@@ -440,7 +440,7 @@ ks_status prologue(const ks_desc *d, const ks_spec *specs, int32_t n_specs, char
                    bool with_range, hipStream_t s, bool uniq = false) {
   // (with the different records, their counts and table follow the ranges)
   const int64_t clear = uniq ? (int64_t)(L.partial - L.range) / 4 : with_range ? 2 * (int64_t)KS_NFAM * d->n_steps : 0;
-  if (!uniq && ks::launch_prologue && d->n_steps <= ks::kPrologueSteps && n_specs <= ks::kPrologueSpecs) {
+  if (!uniq && ks::launch_prologue && ks::prologue_fits(d->n_steps, d->n_req, n_specs)) {
     const hipError_t e = ks::launch_prologue(
         reinterpret_cast<uint32_t *>(ws), reinterpret_cast<uint32_t *>(ws + L.range), clear, specs, n_specs,
         reinterpret_cast<ks::SpecC *>(ws + L.specc), d->req_off, d->req_q, d->req_h, d->n_steps, d->n_req,
