@@ -440,7 +440,7 @@ ks_status prologue(const ks_desc *d, const ks_spec *specs, int32_t n_specs, char
                    bool with_range, hipStream_t s, bool uniq = false) {
   // (with the different records, their counts and table follow the ranges)
   const int64_t clear = uniq ? (int64_t)(L.partial - L.range) / 4 : with_range ? 2 * (int64_t)KS_NFAM * d->n_steps : 0;
-  if (!uniq && ks::launch_prologue && ks::prologue_fits(d->n_steps, d->n_req, n_specs)) {
+  if (!uniq && ks::prologue_fits(d->n_steps, d->n_req, n_specs)) {
     const hipError_t e = ks::launch_prologue(
         reinterpret_cast<uint32_t *>(ws), reinterpret_cast<uint32_t *>(ws + L.range), clear, specs, n_specs,
         reinterpret_cast<ks::SpecC *>(ws + L.specc), d->req_off, d->req_q, d->req_h, d->n_steps, d->n_req,
@@ -594,6 +594,15 @@ size_t ks::eval_workspace_bytes(const int64_t fam_off[KS_NFAM + 1], int64_t n_st
   d.n_rows = fam_off[KS_NFAM];
   d.n_steps = n_steps;
   return layout_of(&d, n_specs).total;
+}
+
+// Replaced, where the kernels are linked, by the launch that does both.
+__attribute__((weak)) hipError_t ks::launch_prologue(uint32_t *err, uint32_t *range, int64_t n_range,
+                                                     const ks_spec *specs, int32_t n_specs, SpecC *out,
+                                                     const uint32_t *req_off, const uint32_t *q, const uint32_t *h,
+                                                     int64_t n_steps, int64_t n_req, uint64_t *agg, hipStream_t s) {
+  const hipError_t e = launch_clear_prep(err, range, n_range, specs, n_specs, out, s);
+  return e != hipSuccess ? e : launch_attn_agg(req_off, q, h, n_steps, n_req, agg, err, s);
 }
 
 ks_status ks::set_error(ks_status st, const char *fmt, ...) {

@@ -251,8 +251,7 @@ hipError_t launch_attn_agg(const uint32_t *req_off, const uint32_t *q, const uin
 hipError_t launch_unique(const UniqParams &p, hipStream_t s);
 // the different records' per-pair values to every record's outputs
 hipError_t launch_spread(const UniqParams &u, const EvalParams &p, hipStream_t s);
-// launch_clear_prep and launch_attn_agg in one launch of one workgroup (weak: a
-// host build that stands in for those two alone has none), for at
+// launch_clear_prep and launch_attn_agg in one launch of one workgroup, for at
 // most kPrologueSpecs specs and few steps and requests: up to 64 steps (one pass
 // of 16 lanes each) 2.4 us a call less than the two, still 1.5 less at 36,000
 // requests, as much at 110,000, 4 more at 145,000; of 65 to 128 steps 1 to 0.3 us
@@ -262,7 +261,7 @@ constexpr int32_t kPrologueSpecs = 1024;
 constexpr bool prologue_fits(int64_t n_steps, int64_t n_req, int32_t n_specs) {
   return n_specs <= kPrologueSpecs && n_steps <= 128 && n_req <= (n_steps <= 64 ? 65536 : 8192);
 }
-__attribute__((weak)) hipError_t launch_prologue(uint32_t *err, uint32_t *range, int64_t n_range, const ks_spec *specs, int32_t n_specs,
+hipError_t launch_prologue(uint32_t *err, uint32_t *range, int64_t n_range, const ks_spec *specs, int32_t n_specs,
                            SpecC *out, const uint32_t *req_off, const uint32_t *q, const uint32_t *h, int64_t n_steps,
                            int64_t n_req, uint64_t *agg, hipStream_t s);
 // the evaluation of a kind's records; with p.uniq, through the different

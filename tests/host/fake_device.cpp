@@ -13,6 +13,8 @@
 //                     t_step = 1e-3 + 2e-7 Q + 1e-4 s + 5e-4 [n_launch > 0]
 //                     (s: the spec index), and t_body = t_gpu = t_step
 //                     and, with own, each step's latency under its own spec
+//   launch_eval       fills every region of the workspace the evaluation may
+//                     write and notes whether they are apart (fake_device.h)
 // and the others do nothing.  The stand-in latency is not the model: the
 // driver prices schedules with it so that the oracle's scheduler, given the
 // same function, must form the same batches.
@@ -20,7 +22,9 @@
 
 #include <cstdlib>
 #include <cstring>
+#include <vector>
 
+#include "fake_device.h"
 #include "ks_internal.h"
 
 extern "C" {
@@ -81,7 +85,68 @@ hipError_t launch_attn_agg(const uint32_t *req_off, const uint32_t *q, const uin
   return hipSuccess;
 }
 
-hipError_t launch_eval(int, const EvalParams &, hipStream_t) { return hipSuccess; }
+// Fills a region of the workspace; fill_check then sees whether another overlaps it.
+struct Filled {
+  unsigned char *p;
+  size_t n;
+  unsigned char v;
+};
+static std::vector<Filled> filled;
+
+template <class T>
+static void fill(const T *p, size_t n) {
+  filled.push_back({reinterpret_cast<unsigned char *>(const_cast<T *>(p)), n * sizeof(T), (unsigned char)(filled.size() + 1)});
+  std::memset(filled.back().p, filled.back().v, filled.back().n);
+}
+
+static bool fill_check() {
+  bool ok = true;
+  for (const Filled &f : filled)
+    for (size_t i = 0; i < f.n; ++i) ok = ok && f.p[i] == f.v;
+  filled.clear();
+  return ok;
+}
+
+// What the last evaluation was asked for: whether it takes the different
+// records, of which families, and whether the regions it may write are apart.
+EvalSeen eval_seen;
+
+// Writes everything an evaluation may write in the workspace.
+hipError_t launch_eval(int, const EvalParams &p, hipStream_t) {
+  eval_seen = EvalSeen{p.uniq != nullptr, p.uniq_mask, p.uniq && p.uniq->pair, true};
+  const size_t S = (size_t)p.n_specs, J = (size_t)p.n_steps;
+  fill(p.spec_c, S);
+  if (p.range) fill(p.range, 2 * KS_NFAM * J);
+  if (p.partial) fill(p.partial, KS_NFAM * J * S);
+  if (p.carry) fill(p.carry, (size_t)p.n_tiles * S);
+  if (p.uniq) {
+    const UniqParams &u = *p.uniq;
+    const size_t chunks = (size_t)u.chunk_off[KS_NFAM];
+    size_t records = 0, slots = 0, entries = 0;
+    for (int f = 0; f < KS_NFAM; ++f) {
+      records += u.cap[f];
+      slots += u.slots[f];
+      entries += (size_t)(u.chunk_off[f + 1] - u.chunk_off[f]) * u.chunk_entries[f];
+    }
+    if (!p.range) fill(u.dir, 2 * KS_NFAM * J);
+    fill(u.count, KS_NFAM);
+    fill(u.over, 1);
+    fill(u.chunk_count, chunks);
+    fill(u.list, records);
+    fill(u.slot_row, slots);
+    fill(u.slot_id, slots);
+    fill(u.ent, entries);
+    fill(u.ent_slot, entries);
+    fill(p.u_t, records * S);
+    if (u.pair) {
+      fill(p.u_t + p.u_pair, records * S);
+      fill(p.u_t + 2 * p.u_pair, records * S);
+      fill(u.row_entry, chunks * kUniqChunk);
+    }
+  }
+  eval_seen.apart = fill_check();
+  return hipSuccess;
+}
 
 hipError_t launch_finish(const FinishParams &p, hipStream_t) {
   for (int32_t s = 0; s < p.n_specs; ++s)

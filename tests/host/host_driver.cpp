@@ -9,6 +9,9 @@
 //                      with the stand-in step latency; prints each
 //                      simulation's steps and per-request metrics with
 //                      exact (hexadecimal) floats
+//   host_driver route  reads calls on stdin (steps, spec vectors, head, outputs,
+//                      bounded mask, workspace, records per family) and prints
+//                      what each call's evaluation is asked for
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
@@ -17,6 +20,7 @@
 #include <string>
 #include <vector>
 
+#include "fake_device.h"
 #include "ks.h"
 
 namespace {
@@ -398,11 +402,72 @@ int run_sim() {
   return 0;
 }
 
+// Per call: "steps specs precision in_dim hidden bounded_mask outs short" then
+// ten record counts; outs 0: step sums, 1: and t_kernel, 2: and the counts, 3:
+// per-pair outputs without step sums; short 1: a workspace with no room for the
+// different records.  The record arrays are never read on the host.
+int run_route() {
+  long long J;
+  int S, precision, in_dim, hidden, outs, shrt;
+  unsigned mask;
+  std::vector<float> params(64);
+  while (std::scanf("%lld %d %d %d %d %u %d %d", &J, &S, &precision, &in_dim, &hidden, &mask, &outs, &shrt) == 8) {
+    ks_desc d;
+    std::memset(&d, 0, sizeof d);
+    for (int f = 0; f < KS_NFAM; ++f) {
+      long long n;
+      if (std::scanf("%lld", &n) != 1) return 2;
+      d.fam_off[f + 1] = d.fam_off[f] + n;
+    }
+    d.n_rows = d.fam_off[KS_NFAM];
+    std::vector<uint32_t> one(1, 0), off((size_t)J + 1, 0), per_step((size_t)J, 1);
+    d.step = d.m = d.n = d.k = d.a = d.b = one.data();
+    d.n_steps = J;
+    d.req_off = off.data();
+    d.elem_bytes = 2;
+    ks_steps st{J, per_step.data(), per_step.data(), per_step.data(), per_step.data()};
+    std::vector<ks_spec> specs((size_t)S, ks_spec{1e15, 4e12, 3e-6, 5e7, 8e-6, 2e-6, 3e11, 132u, 0u});
+    ks_heads h;
+    std::memset(&h, 0, sizeof h);
+    h.precision = precision;
+    h.in_dim = in_dim;
+    h.hidden = hidden;
+    h.w1 = h.w2 = h.b2 = h.w3 = h.b3 = params.data();
+    h.bounded_mask = mask;
+    h.bounded = mask ? params.data() : nullptr;
+    ks_host host{4e-6, 0.0, 0.0, 0.0, 1.0};
+    std::vector<double> so(3 * (size_t)J * (size_t)S);
+    ks_step_out sum{so.data(), so.data() + (size_t)J * (size_t)S, so.data() + 2 * (size_t)J * (size_t)S};
+    ks_kernel_out ko;
+    std::memset(&ko, 0, sizeof ko);
+    if (outs) ko.t_kernel = params.data();
+    if (outs == 2) ko.flops = reinterpret_cast<uint64_t *>(params.data());
+    size_t wsb = ks_workspace_bytes(&d, S);
+    if (shrt) {
+      // up to the carries: as large as without the different records
+      auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+      size_t tiles = 0;
+      for (int f = 0; f < KS_NFAM; ++f) tiles += (size_t)(d.fam_off[f + 1] - d.fam_off[f] + 63) / 64;
+      wsb = 256 + up(64 * (size_t)S) + up(32 * (size_t)J) + up(80 * (size_t)J) + up(80 * (size_t)J * (size_t)S) +
+            up(8 * (size_t)S * tiles);
+    }
+    void *ws = std::aligned_alloc(256, wsb);   // to the byte: a write past its end is reported
+    const ks_status r = outs == 3 ? ks_eval_kernels(&d, specs.data(), S, &h, &ko, ws, wsb, nullptr)
+                                  : ks_eval_steps(&d, &st, specs.data(), S, &h, &host, &sum, outs ? &ko : nullptr, ws, wsb,
+                                                  nullptr);
+    std::free(ws);
+    std::printf("status %d uniq %d mask %u pair %d apart %d bytes %zu\n", (int)r, (int)ks::eval_seen.uniq,
+                ks::eval_seen.mask, (int)ks::eval_seen.pair, (int)ks::eval_seen.apart, wsb);
+  }
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   if (argc == 2 && std::string(argv[1]) == "args") return run_args();
   if (argc == 2 && std::string(argv[1]) == "sim") return run_sim();
-  std::fprintf(stderr, "usage: host_driver args|sim\n");
+  if (argc == 2 && std::string(argv[1]) == "route") return run_route();
+  std::fprintf(stderr, "usage: host_driver args|sim|route\n");
   return 2;
 }

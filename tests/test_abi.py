@@ -32,6 +32,14 @@ def test_library_exports_every_declared_symbol():
     assert abi.ks_version().startswith("ks ")
 
 
+def test_launches_are_the_kernels_own():
+    """The library's launches are the kernels' definitions, not the host code's
+    weak stand-ins."""
+    out = subprocess.run(["nm", "-D", "--defined-only", abi.load()._name], capture_output=True, text=True, check=True)
+    kinds = {w[2]: w[1] for w in (line.split() for line in out.stdout.splitlines()) if "launch_prologue" in w[2]}
+    assert kinds and set(kinds.values()) == {"T"}, kinds
+
+
 def test_struct_layout_matches_header(tmp_path):
     """Compile a C probe of offsetof/sizeof against include/ks.h and compare
     with the ctypes mirrors."""

@@ -184,3 +184,35 @@ def test_host_simulator_matches_oracle_scheduler(driver, case):
         np.testing.assert_array_equal([x[3] for x in got["req"]], ref.e2e)
     if case in ("tight", "lockstep"):
         assert sims[0]["preemptions"] > 0
+
+
+LAYERS = 32
+# records per step and family of a 32-layer dense decoder and of a mixture of
+# experts, a record per kernel and the layers collapsed
+DENSE = (4 * LAYERS, 1, 0, 0, LAYERS, 2 * LAYERS, LAYERS, LAYERS, 0, 1)
+FLAT = (4, 1, 0, 0, 1, 2, 1, 1, 0, 1)
+MOE = (3 * LAYERS, 1, 2 * LAYERS, 0, LAYERS, 2 * LAYERS, LAYERS, LAYERS, 0, 1)
+
+
+def _route(driver, steps, specs, per_step, head=(1, 16, 128), bounded=0, outs=0, short=0):
+    line = f"{steps} {specs} {head[0]} {head[1]} {head[2]} {bounded} {outs} {short} "
+    line += " ".join(str(n * steps) for n in per_step)
+    t = _run(driver, "route", line + "\n").split()
+    return {k: int(v) for k, v in zip(t[::2], t[1::2])}
+
+
+@pytest.mark.parametrize("steps,specs,per_step", [(1000, 64, DENSE), (1, 2000, DENSE), (20001, 33, FLAT), (777, 300, MOE),
+                                                  (5000, 130, (0,) * 9 + (1,))])
+@pytest.mark.parametrize("outs", [0, 1, 2, 3])
+def test_host_different_records_stay_in_the_workspace(driver, steps, specs, per_step, outs):
+    """Every region a call may write lies in a workspace of ks_workspace_bytes and
+    overlaps no other, with the different records and, in a workspace with no
+    room for them, without."""
+    head = (0, 32, 128)
+    r = _route(driver, steps, specs, per_step, head, outs=outs)
+    assert r["status"] == KS_OK and r["apart"] == 1
+    taken = sum(1 << f for f, n in enumerate(per_step) if n and f != gen.GROUPED_GEMM)
+    assert (r["uniq"], r["mask"], r["pair"]) == (1, taken, int(outs > 0))
+    s = _route(driver, steps, specs, per_step, head, outs=outs, short=1)
+    assert s["bytes"] < r["bytes"]
+    assert (s["status"], s["uniq"], s["mask"], s["apart"]) == (KS_OK, 0, 0, 1)
