@@ -32,8 +32,8 @@ def test_request_sums_around_the_prologue_rule(n_steps, per_step, n_specs):
     np.testing.assert_array_equal(out["bytes"], 2 * (2 * H * d * q.sum(1) + 2 * Hkv * d * (q + h).sum(1)))
     np.testing.assert_array_equal(out["blocks"], H * ((q + 127) // 128).sum(1))
     sp = wl.specs
-    W = -(-out["blocks"][None] // sp["n_cu"][:, None].astype(np.uint64)).astype(np.float64)
-    u = W * sp["n_cu"][:, None] / out["blocks"][None]
+    B, N = out["blocks"].astype(np.int64)[None], sp["n_cu"].astype(np.int64)[:, None]
+    u = ((B + N - 1) // N * N) / B
     t = np.maximum(np.maximum(out["flops"][None] * u / sp["peak_flops"][:, None], out["bytes"][None] / sp["hbm_bw"][:, None]),
                    sp["t0"][:, None])
     assert g.rel_err(out["t_kernel"], t).max() <= 1e-5
