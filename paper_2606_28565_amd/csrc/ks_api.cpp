@@ -59,7 +59,8 @@ constexpr size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 //   carry   : n_tiles * n_specs double (spec-minor)
 // and, where the different records are evaluated instead of all (uniq_plan):
 //   ctl     : 256 B, right after range (cleared with it): their count per
-//             family [KS_NFAM] and, at word 15, the flag that they did not fit
+//             family [KS_NFAM] and, from word 16, a flag per family that they
+//             did not fit
 //   rows    : uint32 per table slot: a record's row + 1 (cleared with range)
 //   slot    : uint32 per table slot, after carry: its index
 //   count   : uint32 per chunk: its entries
@@ -85,18 +86,22 @@ constexpr double kUniqPairs = kUniqF32Flops / (2.0 * 128 * (32 + 128));
 
 // The different records of a call: which families, and the room for their
 // entries and records.  A family of at most kFlatPerStep records per step gets
-// room for all of them; a larger one (a record per layer) a quarter of its
-// records as entries and the different records of four kernels per layer, one
-// step at a time, with a margin (when they do not fit, every record is
-// evaluated).  Grouped GEMMs stay out: each layer has its own routed rows.
-constexpr int64_t kFlatPerStep = 8;
-constexpr int kUniqOver = 15;
+// room for all of them.  A larger one (a record per layer) gets the different
+// records of four kernels per layer, one step at a time, with a margin: a chunk
+// has four entries per piece, a step has a piece and one more for each chunk it
+// runs on into, so 4 n_steps + 4 rows / 1024 hold them, and 28 more per chunk make
+// 4 n_steps + rows / 32.  Entry slots: up to kDensePerStep records per step all
+// of a chunk's (four entries per piece of 17 and more stay below 256), else a
+// quarter.  A family whose records do not fit is evaluated record by record, the
+// others not.  Grouped GEMMs stay out: each layer has its own routed rows.
+constexpr int64_t kFlatPerStep = 8, kDensePerStep = 17;
+constexpr int kUniqOver = 16;
 
 struct UniqPlan {
   uint32_t mask = 0;
   bool rest = false;   // grouped GEMMs, or a family that might not fit
   int32_t chunk_off[KS_NFAM + 1];
-  uint32_t chunk_entries[KS_NFAM], ent_off[KS_NFAM], base[KS_NFAM], cap[KS_NFAM];
+  uint32_t chunk_entries[KS_NFAM], spare[KS_NFAM], ent_off[KS_NFAM], base[KS_NFAM], cap[KS_NFAM];
   uint32_t slot_off[KS_NFAM], slots[KS_NFAM], slot_mask[KS_NFAM];
   int32_t scan_off[KS_NFAM + 1], unit_off[KS_NFAM + 1];
   uint32_t entries = 0, records = 0, all_slots = 0;
@@ -113,8 +118,10 @@ bool uniq_plan(const ks_desc *d, int32_t n_specs, UniqPlan *pl) {
     pl->chunk_off[f] = (int32_t)chunks;
     pl->ent_off[f] = (uint32_t)ent;
     pl->base[f] = (uint32_t)rec;
-    pl->chunk_entries[f] = flat ? ks::kUniqChunk : ks::kUniqChunk / 4;
+    const bool dense = flat || rows <= kDensePerStep * d->n_steps;
+    pl->chunk_entries[f] = dense ? ks::kUniqChunk : ks::kUniqChunk / 4;
     pl->cap[f] = (uint32_t)(flat || rows < room ? rows : room);
+    pl->spare[f] = flat || rows < room ? ks::kUniqChunk : 28;
     if (rows > 0) pl->mask |= 1u << f;
     pl->rest = pl->rest || !flat || (f == KS_GROUPED_GEMM && d->fam_off[f + 1] > d->fam_off[f]);
     // the table: a slot per step for attention; for a dense family twice its
@@ -135,7 +142,7 @@ bool uniq_plan(const ks_desc *d, int32_t n_specs, UniqPlan *pl) {
     pl->unit_off[f] = (int32_t)units;
     slots += ns;
     scans += (ns + ks::kUniqScan - 1) / ks::kUniqScan;
-    units += flat ? 4 * n : (n + 3) / 4;
+    units += dense ? 4 * n : (n + 3) / 4;
     if (slots >= (int64_t(1) << 30)) return false;
     chunks += n;
     ent += n * pl->chunk_entries[f];
@@ -421,6 +428,7 @@ void fill_uniq(ks::UniqParams &u, ks::EvalParams &p, const ks_desc *d, int32_t n
     u.fam_off[f] = p.fam_off[f];
     u.chunk_off[f] = pl.chunk_off[f];
     u.chunk_entries[f] = pl.chunk_entries[f];
+    u.spare[f] = pl.spare[f];
     u.ent_off[f] = pl.ent_off[f];
     u.slot_off[f] = pl.slot_off[f];
     u.slots[f] = pl.slots[f];

@@ -108,8 +108,14 @@ __global__ __launch_bounds__(kFinThreads) void k_finish(FinishParams p, int spec
 }
 
 // ------------------------------------------------------------ different records
+// The families whose different records were evaluated (by whole waves).
+__device__ __forceinline__ uint32_t families_taken(const FinishParams &p) {
+  const int lane = threadIdx.x & 63;
+  return (uint32_t)__ballot(lane < KS_NFAM && ((p.uniq_mask >> lane) & 1u) && !p.u_over[lane < KS_NFAM ? lane : 0]);
+}
+
 // The body's terms of one family that the evaluation kernel summed itself
-// (grouped GEMMs; every family when the different records did not fit): the
+// (grouped GEMMs, and families whose different records did not fit): the
 // partial, then the carries of its later tiles.
 __device__ __forceinline__ double direct_sum(const FinishParams &p, int f, uint32_t r0, uint32_t r1, int64_t j, int s) {
   const int64_t base = p.fam_off[f], top = p.fam_off[f + 1];
@@ -176,7 +182,7 @@ template <int NS>
 __global__ __launch_bounds__(kFinThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_finish_few(FinishParams p) {
   __shared__ double part[kFewSteps][KS_NFAM][NS];
   const int tid = threadIdx.x, f = tid & 15, jj = tid >> 4;
-  const uint32_t uniq = p.u_over[0] == 0 ? p.uniq_mask : 0u;
+  const uint32_t uniq = families_taken(p);
   const int64_t n_st = (p.n_steps + kFewSteps - 1) / kFewSteps;
   for (int64_t tile = blockIdx.x; tile < n_st; tile += gridDim.x) {
     const int64_t j0 = tile * kFewSteps, j = j0 + jj;
@@ -229,7 +235,7 @@ __global__ __launch_bounds__(kFinThreads) void k_finish_list(FinishParams p, int
   __shared__ uint2 list[kListSteps][KS_NFAM * kListEntries];
   __shared__ uint32_t count[kListSteps * KS_NFAM];
   __shared__ uint32_t total[kListSteps], rest[kListSteps];        // rest: families with more entries or sums of their own
-  const uint32_t uniq = p.u_over[0] == 0 ? p.uniq_mask : 0u;
+  const uint32_t uniq = families_taken(p);
   const int tps = 1 << spec_bits;
   const int tst = min(kFinThreads >> spec_bits, kListSteps);
   const int64_t n_st = (p.n_steps + tst - 1) / tst;

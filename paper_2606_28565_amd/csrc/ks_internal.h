@@ -64,6 +64,7 @@ struct UniqParams {
   int64_t fam_off[KS_NFAM + 1];
   int32_t chunk_off[KS_NFAM + 1];      // chunks of the families taken (none for the others)
   uint32_t chunk_entries[KS_NFAM];     // entry slots of a chunk
+  uint32_t spare[KS_NFAM];             // entries a chunk may have beyond four per piece
   uint32_t ent_off[KS_NFAM];           // a family's first entry
   uint32_t base[KS_NFAM], cap[KS_NFAM];
   uint32_t slot_off[KS_NFAM], slots[KS_NFAM], slot_mask[KS_NFAM];   // a family's table (attention: a slot per step)
@@ -74,7 +75,8 @@ struct UniqParams {
   bool rest;                           // host only: some records may be evaluated without it
   UniqEntry *ent;
   uint32_t *dir;        // [KS_NFAM][n_steps][2]: first entry + 1, end row (zero: no such records)
-  uint32_t *list, *count, *over;
+  uint32_t *list, *count;
+  uint32_t *over;          // [KS_NFAM] nonzero: a family's did not fit, all its records are evaluated
   uint32_t *chunk_count;   // entries of each chunk
   uint32_t *slot_row;      // a slot's record: row + 1, or 0
   uint32_t *slot_id;       // ... and its index among the different records
@@ -123,8 +125,8 @@ struct EvalParams {
   uint32_t *err;
   // the different records (k_unique), for the families of uniq_mask: k_eval's
   // unique-record variant evaluates u_list[u_base[f] + i], i < u_count[f], and
-  // stores t at u_t[(u_base[f] + i) n_specs + spec].  u_over: nonzero when they
-  // did not fit; that variant then evaluates every record.
+  // stores t at u_t[(u_base[f] + i) n_specs + spec].  u_over[f]: nonzero when a
+  // family's did not fit; that variant then evaluates its every record.
   const UniqParams *uniq;      // host pointer, read by launch_eval only (nullptr: every record is evaluated)
   uint32_t uniq_mask;
   const uint32_t *u_list, *u_count, *u_over;

@@ -1439,8 +1439,8 @@ __device__ __forceinline__ void tile_edges(const Tile &t, const Fields &f, uint3
 // kVarMult weights each record's step-sum term by its multiplicity, kVarUniq
 // takes the different records k_unique found (each one's t for every spec is
 // stored, no step sums or per-pair outputs) and, with kVarRest, beside them
-// every record of the families left out (all families when the different
-// records did not fit): one launch, whose parts fill each other's last round
+// every record of the families left out (grouped GEMMs, and those whose
+// different records did not fit): one launch, whose parts fill each other's last round
 // (MoE trace 61 -> 54 us), but the code of both (homogeneous 70B trace, where
 // nothing is left out: 46 us with it, 39 without).
 enum : int { kVarGrid = 1, kVarMult = 2, kVarUniq = 4, kVarRest = 2, kNumVars = 8 };
@@ -1490,8 +1490,7 @@ struct UniqTiles {
 // took 5 to 10 us, with its divisions in a row).
 __device__ __forceinline__ void uniq_tiles(const EvalParams &p, int grid, UniqTiles &u) {
   const int lane = threadIdx.x & 63, f = lane < KS_NFAM ? lane : 0;
-  const uint32_t mask = p.u_over[0] ? 0u : p.uniq_mask;
-  const bool on = (mask >> f) & 1u;
+  const bool on = ((p.uniq_mask >> f) & 1u) && !p.u_over[f];
   const int cnt = lane < KS_NFAM && on ? (int)min(p.u_count[f], p.u_cap[f]) : 0;
   const int t64 = (cnt + kTileRows - 1) / kTileRows;
   int rest = lane < KS_NFAM && !on ? p.wgt_off[f + 1] - p.wgt_off[f] : 0, tiles = t64, all = rest;
@@ -2521,12 +2520,11 @@ void k_stream(EvalParams p) {
 // The exact counts of the records whose latency another record's evaluation
 // gave (the families of uniq_mask): HBM-bound, a row per thread.
 __global__ void k_counts(EvalParams p) {
-  if (p.u_over[0]) return;
   const int64_t n_rows = p.fam_off[KS_NFAM];
   int f = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * blockDim.x) {
     while (i >= p.fam_off[f + 1]) ++f;
-    if (!((p.uniq_mask >> f) & 1u)) continue;
+    if (!((p.uniq_mask >> f) & 1u) || p.u_over[f]) continue;
     const bool attn = f == KS_ATTN_PREFILL || f == KS_ATTN_DECODE;
     uint32_t bad = 0;
     const Cnt c = record_counts(f, attn ? 0u : p.m[i], p.n[i], uses_k(f) ? p.k[i] : 0u, attn ? p.a[i] : 0u, 0u,

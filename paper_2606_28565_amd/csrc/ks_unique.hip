@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kUqThreads) __attribute__((amdgpu_waves_per_eu(8)))
   }
   if (flag) {
     atomicOr(p.err, flag);
-    if (p.pair) p.over[0] = 1u;
+    if (p.pair) p.over[f] = 1u;
   }
   uint32_t piece = 0;
   {
@@ -252,9 +252,12 @@ __global__ __launch_bounds__(kUqThreads) __attribute__((amdgpu_waves_per_eu(8)))
   __syncthreads();
   uint32_t n_ent;
   uint32_t e0 = waves_before(sh.entries, n_ent) + incl - sum;
+  // no room: in the chunk, or for the family's different records (which a rule
+  // on each chunk's entries keeps below the family's room, so that it does not
+  // hang on which of the records that share a slot was stored last)
   const uint32_t slots = p.chunk_entries[f];
-  if (n_ent > slots) {
-    if (tid == 0) p.over[0] = 1u;
+  if (n_ent > min(slots, 4u * n_pieces + p.spare[f])) {
+    if (tid == 0) p.over[f] = 1u;
     return;
   }
   const uint32_t ent0 = p.ent_off[f] + (uint32_t)(c - p.chunk_off[f]) * slots;
@@ -311,10 +314,11 @@ __device__ __forceinline__ UniqKey key_of(const UniqParams &p, int f, uint32_t r
 }
 
 // Room for n new different records of family f: their first index among the
-// family's (past the family's room: the call falls back to every record).
+// family's (past its room, where unsorted steps make more pieces than steps: all
+// its records are evaluated).
 __device__ __forceinline__ uint32_t take_records(const UniqParams &p, int f, uint32_t n) {
   const uint32_t i = atomicAdd(p.count + f, n);
-  if (i + n > p.cap[f]) p.over[0] = 1u;
+  if (i + n > p.cap[f]) p.over[f] = 1u;
   return i;
 }
 
@@ -366,7 +370,7 @@ __global__ __launch_bounds__(kUqThreads) void k_join(UniqParams p) {
   while (u >= p.unit_off[f + 1]) ++f;
   const bool flat = p.chunk_entries[f] == kUniqChunk;
   const int local = u - p.unit_off[f], c = flat ? local / 4 : 4 * local + (lane >> 4);
-  if (p.over[0]) return;   // (a chunk without room wrote no count)
+  if (p.over[f]) return;   // (a chunk without room wrote no count)
   const uint32_t e0 = flat ? (uint32_t)(local % 4) * (kUniqChunk / 4) : 0u, step = flat ? 64 : 16;
   const uint32_t ent0 = p.ent_off[f] + (uint32_t)c * p.chunk_entries[f];
   const uint32_t n = c < p.chunk_off[f + 1] - p.chunk_off[f] ? p.chunk_count[p.chunk_off[f] + c] : 0u;
@@ -420,11 +424,11 @@ __global__ __launch_bounds__(kUqThreads) void k_spread(UniqParams u, const float
                                                        int64_t n_rows, float *o_troof, float *o_eta, float *o_t,
                                                        uint32_t total, uint32_t all_slots, int per_range) {
   __shared__ uint32_t rec[kUniqChunk];
-  if (u.over[0]) return;   // every record was evaluated
   typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
   const int tid = threadIdx.x, c = (int)blockIdx.x;
   int f = 0;
   while (c >= u.chunk_off[f + 1]) ++f;
+  if (u.over[f]) return;   // its every record was evaluated
   const int64_t row0 = u.fam_off[f] + (int64_t)(c - u.chunk_off[f]) * kUniqChunk;
   const int64_t left = u.fam_off[f + 1] - row0;
   const int n = left < kUniqChunk ? (int)left : kUniqChunk;

@@ -37,3 +37,62 @@ def test_request_sums_around_the_prologue_rule(n_steps, per_step, n_specs):
     t = np.maximum(np.maximum(out["flops"][None] * u / sp["peak_flops"][:, None], out["bytes"][None] / sp["hbm_bw"][:, None]),
                    sp["t0"][:, None])
     assert g.rel_err(out["t_kernel"], t).max() <= 1e-5
+
+
+def _steps(wl, room):
+    """Step sums, the device status and, with room, the families whose different
+    records did not fit (a flag each, from word 16 after the record ranges)."""
+    import torch
+    di = abi.DeviceInputs(wl)
+    up = lambda x: -(-x // 256) * 256
+    S, N = wl.desc.n_steps, di.n_specs
+    ctl = 256 + up(64 * N) + up(32 * S) + up(80 * S)
+    tiles = sum(-(-int(k) // 64) for k in np.diff(wl.desc.fam_off))
+    small = ctl + up(80 * N * S) + up(8 * N * tiles)
+    assert small < di.ws_bytes
+    so_t, so = abi.step_outputs(S, N)
+    abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, N, di.heads, di.host, so, None, di.ws_ptr,
+                      di.ws_bytes if room else small, abi.current_stream())
+    torch.cuda.synchronize()
+    st = abi.ks_device_status(di.ws_ptr, di.ws_bytes, abi.current_stream(), check=False)
+    o = ctl + di.ws_ptr - di.ws.data_ptr() + 64
+    over = di.ws[o:o + 4 * gen.NFAM].view(torch.int32).cpu().numpy()
+    return {k: v.cpu().numpy() for k, v in so_t.items()}, st, [f for f in range(gen.NFAM) if over[f]]
+
+
+def _layers(kernels, layers, n_steps, odd_step=None):
+    """Steps of `layers` repeats of `kernels` GEMMs (one step without repeats),
+    norms that repeat and grouped-free rest."""
+    rows = []
+    for j in range(n_steps):
+        m = 3 + 7 * (j % 50)
+        n = kernels * layers
+        rows += [(gen.GEMM, j, m, 64 * (1 + (i if j == odd_step else i % kernels)), 256, 0, 0) for i in range(n)]
+        rows += [(gen.RMSNORM, j, m, 4096, 0, 0, 0)] * (2 * layers) + [(gen.LM_HEAD, j, 1 + j % 9, 32000, 4096, 0, 0)]
+    return rows
+
+
+@pytest.mark.parametrize("precision,in_dim,hidden", [("bf16", 16, 128), ("bf16", 32, 256), ("f32", 32, 128)])
+@pytest.mark.parametrize("kernels,layers,odd,over", [(4, 3, None, []), (3, 3, None, []), (4, 4, None, []), (4, 5, None, []),
+                                                     (5, 3, None, [gen.GEMM]), (5, 40, None, [gen.GEMM]), (4, 40, None, []),
+                                                     (4, 8, 77, []), (4, 60, 77, [gen.GEMM])])
+def test_a_family_that_does_not_fit_leaves_the_others(precision, in_dim, hidden, kernels, layers, odd, over):
+    """Up to four kernels per layer fit at any number of layers (three layers of
+    four are twelve records per step, three entries per eight records); a family of
+    five, or with a long step without repeats, is evaluated record by record, and
+    only that one.  One step without repeats fits where its entries do (32 here,
+    28 more than four).  The reference evaluates every record: fp32 sums within 64-record tiles
+    (6 levels of adds) against float64 ones: 6 2^-24."""
+    n_steps = max(600, 9000 // (kernels * layers))
+    rows = _layers(kernels, layers, n_steps, odd)
+    n_specs = 24 if precision == "f32" else 160
+    wl = gen.Workload("layers", make_desc(rows, [[(1 + j % 7, 5)] for j in range(n_steps)]), steprec(n_steps),
+                      gen.specs_grid(n_specs, 5), gen.make_heads(in_dim, hidden, precision), gen.HostConsts())
+    ref, _, _ = _steps(wl, False)
+    got, st, seen = _steps(wl, True)
+    assert st == abi.KS_OK and seen == over
+    for k in ref:
+        np.testing.assert_allclose(got[k], ref[k], rtol=6 * 2.0 ** -24)
+    again, _, _ = _steps(wl, True)
+    for k in got:
+        np.testing.assert_array_equal(again[k], got[k])
