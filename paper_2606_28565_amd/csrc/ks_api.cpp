@@ -76,13 +76,35 @@ struct Layout {
   size_t entry, total;                                    // total: and per-pair outputs (base without them)
 };
 
-// The head work of every record from which finding the different ones pays:
-// 20 us at the rate the heads reach on the whole chip (fp32 140 TFLOP/s, bf16
-// 1.2 PFLOP/s).  Below it the two more kernels (8 us each at any size) cost
-// more than the evaluation.
-constexpr double kUniqF32Flops = 2.8e9, kUniqBf16Flops = 2.4e10;
-// (pairs of records and spec vectors that no head turns into that much work)
-constexpr double kUniqPairs = kUniqF32Flops / (2.0 * 128 * (32 + 128));
+// What evaluating only the different records saves and costs, in seconds, from
+// whole calls of 7B traces timed both ways (hidden 64, 128 and 256, fp32 and bf16;
+// a record per layer and layers collapsed; 2 and 48 specs; sums, t_kernel, every
+// output; 5 to 130 us of head work).
+//
+// Saved: the heads' work at the rate they reach on the whole chip, 5.2 ps per pair
+// of a family on the bounded head; of a family with few records per step, which
+// repeat from step to step only, three quarters.  Rows that are evaluated anyway
+// (grouped GEMMs) save nothing: counted as head work, they made a collapsed
+// mixture of experts' 8000 steps 81 us where evaluating every record takes 65.
+// Cost: 19 us for the kernels that find the records and the longer step sums
+// (sums at 20 us of layers' work 34 to 36 us both ways, at 13 us 28 to 33
+// directly and 34 to 35 so, at 30 us 41 to 48 and 35); with per-pair outputs 7
+// more and the spread of their bytes (collapsed layers' records share little of
+// a cache line), and 5 with counts.  Of 507 calls timed both ways, 497 take the
+// faster route or one within 6% of it (with the work of all records against 20
+// us, three times that with per-pair outputs, 50 of 441 did not); the others
+// come within 16%, and 1000 steps of a collapsed mixture of experts for 16 specs
+// (hidden 256) 30%.
+constexpr double kUniqSecs = 19e-6, kUniqPairSecs = 7e-6, kUniqCountSecs = 5e-6;
+constexpr double kUniqBounded = 5.2e-12, kUniqFew = 0.75;
+constexpr double kUniqSpreadFew = 1.5e12, kUniqSpread = 2.5e12;
+// (the most a pair can save: fp32 heads 32-128)
+constexpr double kUniqF32Rate = 1.9e14, kUniqMost = 2.0 * 128 * (32 + 128) / kUniqF32Rate;
+
+double head_rate(const ks_heads *h) {
+  if (h->precision == KS_F32) return kUniqF32Rate;
+  return h->hidden == 64 ? 0.65e15 : 1.2e15;
+}
 
 // The different records of a call: which families, and the room for their
 // entries and records.  A family of at most kFlatPerStep records per step gets
@@ -108,7 +130,8 @@ struct UniqPlan {
 };
 
 bool uniq_plan(const ks_desc *d, int32_t n_specs, UniqPlan *pl) {
-  if ((double)d->n_rows * n_specs < kUniqPairs) return false;
+  const int64_t taken = d->n_rows - (d->fam_off[KS_GROUPED_GEMM + 1] - d->fam_off[KS_GROUPED_GEMM]);
+  if ((double)taken * n_specs * kUniqMost < kUniqSecs) return false;
   int64_t ent = 0, rec = 0, chunks = 0, slots = 0, scans = 0, units = 0;
   for (int f = 0; f < KS_NFAM; ++f) {
     const int64_t rows = f == KS_GROUPED_GEMM ? 0 : d->fam_off[f + 1] - d->fam_off[f];
@@ -370,18 +393,25 @@ void fill_eval(ks::EvalParams &p, const ks_desc *d, const ks_spec *specs, int32_
 }
 
 // Whether a call evaluates only its different records: MLP heads, given the
-// workspace for it, and enough head work; three times as much with per-pair
-// outputs, which one or two more kernels spread (a 7B trace of 2.1 times the line
-// takes 54 us spread and 50 us directly).  (Their sources come with the direct
-// evaluation of a grid.)
+// workspace for it, and more saved than it costs.  (Per-pair sources come with
+// the direct evaluation of a grid.)
 bool takes_uniq(const ks_desc *d, int32_t n_specs, const ks_heads *h, int kind, const ks_kernel_out *kout,
                 size_t ws_bytes, UniqPlan *pl, Layout *L, bool *pair) {
   if (kind == ks::kEtaOne || kind == ks::kBoundedOnly || d->n_rows == 0) return false;
   *pair = kout && (kout->t_roof || kout->eta || kout->t_kernel);
-  const bool out = kout && (*pair || kout->flops || kout->bytes || kout->blocks);
   if (kout && kout->source && h->grid_mask) return false;
-  const double flops = 2.0 * (double)d->n_rows * n_specs * h->hidden * (h->in_dim + h->hidden);
-  if (flops < (out ? 3.0 : 1.0) * (h->precision == KS_F32 ? kUniqF32Flops : kUniqBf16Flops)) return false;
+  const double head = 2.0 * h->hidden * (h->in_dim + h->hidden) / head_rate(h);
+  const int outs = kout ? (kout->t_roof != nullptr) + (kout->eta != nullptr) + (kout->t_kernel != nullptr) : 0;
+  double saved = 0.0, cost = kUniqSecs + (*pair ? kUniqPairSecs : 0.0);
+  if (kout && (kout->flops || kout->bytes || kout->blocks)) cost += kUniqCountSecs;
+  for (int f = 0; f < KS_NFAM; ++f) {
+    const int64_t rows = f == KS_GROUPED_GEMM ? 0 : d->fam_off[f + 1] - d->fam_off[f];
+    const bool few = rows <= kFlatPerStep * d->n_steps;
+    const double pairs = (double)rows * n_specs;
+    saved += (few ? kUniqFew : 1.0) * pairs * (((h->bounded_mask >> f) & 1u) ? kUniqBounded : head);
+    cost += 4.0 * outs * pairs / (few ? kUniqSpreadFew : kUniqSpread);
+  }
+  if (saved < cost) return false;
   if (!uniq_plan(d, n_specs, pl)) return false;
   const Layout full = layout_of(d, n_specs, pl);
   if (ws_bytes < (*pair ? full.total : full.sums)) return false;

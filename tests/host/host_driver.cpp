@@ -403,8 +403,8 @@ int run_sim() {
 }
 
 // Per call: "steps specs precision in_dim hidden bounded_mask outs short" then
-// ten record counts; outs 0: step sums, 1: and t_kernel, 2: and the counts, 3:
-// per-pair outputs without step sums; short 1: a workspace with no room for the
+// ten record counts; outs 0: step sums, 1: and t_kernel, 2: and every other output, 3:
+// t_kernel without step sums; short 1: a workspace with no room for the
 // different records.  The record arrays are never read on the host.
 int run_route() {
   long long J;
@@ -441,7 +441,10 @@ int run_route() {
     ks_kernel_out ko;
     std::memset(&ko, 0, sizeof ko);
     if (outs) ko.t_kernel = params.data();
-    if (outs == 2) ko.flops = reinterpret_cast<uint64_t *>(params.data());
+    if (outs == 2) {
+      ko.t_roof = ko.eta = params.data();
+      ko.flops = ko.bytes = ko.blocks = reinterpret_cast<uint64_t *>(params.data());
+    }
     size_t wsb = ks_workspace_bytes(&d, S);
     if (shrt) {
       // up to the carries: as large as without the different records

@@ -216,3 +216,73 @@ def test_host_different_records_stay_in_the_workspace(driver, steps, specs, per_
     s = _route(driver, steps, specs, per_step, head, outs=outs, short=1)
     assert s["bytes"] < r["bytes"]
     assert (s["status"], s["uniq"], s["mask"], s["apart"]) == (KS_OK, 0, 0, 1)
+
+
+MOE_FLAT = (3, 1, 2 * LAYERS, 0, 1, 2, 1, 1, 0, 1)
+BF16_64, BF16_128, BF16_256, F32_64, F32_128 = (1, 16, 64), (1, 16, 128), (1, 32, 256), (0, 16, 64), (0, 32, 128)
+
+
+# Calls timed both ways, most of them near the crossing: steps, specs, records per
+# step, head, families on the bounded head, outputs (0 sums, 2 every output too, 3
+# t_kernel alone), us with the different records only, us with every record.
+TIMED = [
+    (2828, 2, DENSE, BF16_64, 0, 0, 37, 45), (67, 48, DENSE, BF16_64, 0, 3, 32, 21),
+    (168, 48, DENSE, BF16_64, 0, 3, 34, 38), (2828, 2, DENSE, BF16_64, 0, 2, 58, 50),
+    (6061, 2, DENSE, BF16_64, 0, 2, 76, 83), (1775, 48, FLAT, BF16_64, 0, 0, 40, 34),
+    (4438, 48, FLAT, BF16_64, 0, 0, 50, 55), (42613, 2, FLAT, BF16_64, 0, 3, 48, 32),
+    (28852, 48, FLAT, BF16_64, 0, 2, 279, 249), (785, 2, DENSE, BF16_128, 0, 0, 35, 33),
+    (1683, 2, DENSE, BF16_128, 0, 0, 35, 48), (46, 48, DENSE, BF16_128, 0, 3, 32, 27),
+    (102, 48, DENSE, BF16_128, 0, 3, 34, 46), (1122, 2, DENSE, BF16_128, 0, 2, 48, 39),
+    (2469, 2, DENSE, BF16_128, 0, 2, 56, 62), (1233, 48, FLAT, BF16_128, 0, 0, 43, 39),
+    (2712, 48, FLAT, BF16_128, 0, 0, 48, 59), (29592, 2, FLAT, BF16_128, 0, 3, 47, 35),
+    (3699, 48, FLAT, BF16_128, 0, 2, 85, 76), (8014, 48, FLAT, BF16_128, 0, 2, 134, 156),
+    (112, 2, DENSE, BF16_256, 0, 0, 40, 32), (420, 2, DENSE, BF16_256, 0, 0, 42, 50),
+    (8, 48, DENSE, BF16_256, 0, 3, 37, 30), (17, 48, DENSE, BF16_256, 0, 3, 38, 41),
+    (280, 2, DENSE, BF16_256, 0, 2, 51, 45), (617, 2, DENSE, BF16_256, 0, 2, 53, 64),
+    (308, 48, FLAT, BF16_256, 0, 0, 48, 44), (678, 48, FLAT, BF16_256, 0, 0, 53, 57),
+    (7398, 2, FLAT, BF16_256, 0, 3, 45, 39), (16276, 2, FLAT, BF16_256, 0, 3, 54, 60),
+    (678, 48, FLAT, BF16_256, 0, 2, 71, 59), (1387, 48, FLAT, BF16_256, 0, 2, 84, 96),
+    (471, 2, DENSE, F32_64, 0, 0, 37, 35), (707, 2, DENSE, F32_64, 0, 0, 37, 42),
+    (19, 48, DENSE, F32_64, 0, 3, 34, 27), (43, 48, DENSE, F32_64, 0, 3, 34, 44),
+    (707, 2, DENSE, F32_64, 0, 2, 49, 43), (1414, 2, DENSE, F32_64, 0, 2, 51, 63),
+    (776, 48, FLAT, F32_64, 0, 0, 47, 43), (1139, 48, FLAT, F32_64, 0, 0, 49, 54),
+    (18643, 2, FLAT, F32_64, 0, 3, 47, 42), (37286, 2, FLAT, F32_64, 0, 3, 54, 64),
+    (1553, 48, FLAT, F32_64, 0, 2, 76, 64), (2330, 48, FLAT, F32_64, 0, 2, 80, 92),
+    (117, 2, DENSE, F32_128, 0, 0, 46, 42), (259, 2, DENSE, F32_128, 0, 0, 47, 62),
+    (3, 48, DENSE, F32_128, 0, 3, 41, 34), (14, 48, DENSE, F32_128, 0, 3, 43, 54),
+    (117, 2, DENSE, F32_128, 0, 2, 54, 43), (259, 2, DENSE, F32_128, 0, 2, 56, 63),
+    (194, 48, FLAT, F32_128, 0, 0, 57, 53), (284, 48, FLAT, F32_128, 0, 0, 58, 62),
+    (4660, 2, FLAT, F32_128, 0, 3, 48, 37), (6835, 2, FLAT, F32_128, 0, 3, 49, 56),
+    (129, 48, FLAT, F32_128, 0, 2, 58, 53), (841, 48, FLAT, F32_128, 0, 2, 84, 103),
+    # mixtures of experts: of the collapsed ones' records nine tenths are grouped
+    # GEMMs, which are evaluated every one
+    (300, 2, MOE_FLAT, BF16_128, 0, 0, 38, 21), (1000, 2, MOE_FLAT, BF16_128, 0, 0, 46, 25),
+    (4000, 2, MOE_FLAT, BF16_128, 0, 0, 59, 39), (8000, 2, MOE_FLAT, BF16_128, 0, 0, 81, 65),
+    (3000, 2, MOE, BF16_128, 0, 0, 62, 83), (300, 16, MOE_FLAT, BF16_256, 0, 0, 90, 69),
+    (4000, 2, MOE_FLAT, BF16_256, 0, 0, 112, 97), (1000, 2, MOE, BF16_256, 0, 0, 66, 99),
+    (300, 2, MOE_FLAT, F32_64, 0, 0, 39, 22), (1000, 2, MOE_FLAT, F32_64, 0, 0, 50, 31),
+    (8000, 2, MOE_FLAT, F32_64, 0, 0, 105, 92),
+    # families on the bounded head
+    (300, 2, DENSE, BF16_128, 3, 0, 34, 22), (20000, 2, FLAT, BF16_128, 3, 0, 44, 31),
+    (2000, 2, DENSE, BF16_128, 1020, 0, 35, 39), (300, 2, DENSE, BF16_256, 3, 0, 41, 35),
+    (20000, 2, FLAT, BF16_256, 3, 0, 56, 62), (2000, 2, DENSE, BF16_256, 1020, 0, 42, 87),
+    (300, 2, DENSE, F32_64, 3, 0, 36, 24), (20000, 2, FLAT, F32_64, 3, 0, 46, 36),
+    (2000, 2, DENSE, F32_64, 1020, 0, 36, 50),
+]
+
+
+def test_host_route_is_the_faster_one(driver):
+    """The rule for evaluating the different records only takes the faster route of
+    each timed call, or one within 15% of it."""
+    lines = []
+    for steps, specs, per_step, head, mask, outs, _, _ in TIMED:
+        lines.append(f"{steps} {specs} {head[0]} {head[1]} {head[2]} {mask} {outs} 0 "
+                     + " ".join(str(n * steps) for n in per_step))
+    got = _run(driver, "route", "\n".join(lines) + "\n").splitlines()
+    assert len(got) == len(TIMED)
+    for call, line in zip(TIMED, got):
+        t = line.split()
+        r = {k: int(v) for k, v in zip(t[::2], t[1::2])}
+        assert r["status"] == KS_OK and r["apart"] == 1
+        once, every = call[-2:]
+        assert (once if r["uniq"] else every) <= 1.15 * min(once, every), call

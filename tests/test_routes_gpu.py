@@ -39,9 +39,9 @@ def test_request_sums_around_the_prologue_rule(n_steps, per_step, n_specs):
     assert g.rel_err(out["t_kernel"], t).max() <= 1e-5
 
 
-def _steps(wl, room):
-    """Step sums, the device status and, with room, the families whose different
-    records did not fit (a flag each, from word 16 after the record ranges)."""
+def _steps(wl, room, pairs=False):
+    """Step sums (and t_kernel), the device status and, with room, the families whose
+    different records did not fit (a flag each, from word 16 after the record ranges)."""
     import torch
     di = abi.DeviceInputs(wl)
     up = lambda x: -(-x // 256) * 256
@@ -51,13 +51,14 @@ def _steps(wl, room):
     small = ctl + up(80 * N * S) + up(8 * N * tiles)
     assert small < di.ws_bytes
     so_t, so = abi.step_outputs(S, N)
-    abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, N, di.heads, di.host, so, None, di.ws_ptr,
+    ko_t, ko = abi.kernel_outputs(wl.desc.n_rows, N, counts=False, t_roof=False, eta=False) if pairs else ({}, None)
+    abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, N, di.heads, di.host, so, ko, di.ws_ptr,
                       di.ws_bytes if room else small, abi.current_stream())
     torch.cuda.synchronize()
     st = abi.ks_device_status(di.ws_ptr, di.ws_bytes, abi.current_stream(), check=False)
     o = ctl + di.ws_ptr - di.ws.data_ptr() + 64
     over = di.ws[o:o + 4 * gen.NFAM].view(torch.int32).cpu().numpy()
-    return {k: v.cpu().numpy() for k, v in so_t.items()}, st, [f for f in range(gen.NFAM) if over[f]]
+    return {k: v.cpu().numpy() for k, v in (so_t | ko_t).items()}, st, [f for f in range(gen.NFAM) if over[f]]
 
 
 def _layers(kernels, layers, n_steps, odd_step=None):
@@ -96,3 +97,22 @@ def test_a_family_that_does_not_fit_leaves_the_others(precision, in_dim, hidden,
     again, _, _ = _steps(wl, True)
     for k in got:
         np.testing.assert_array_equal(again[k], got[k])
+
+
+def test_bad_steps_of_one_family_with_per_pair_outputs():
+    """Per-pair outputs of records whose step is out of range come from evaluating
+    every record of their family; the other families' are spread from the different
+    ones.  Both as every record's evaluation gives them."""
+    n_steps = 300
+    rows = _layers(4, 20, n_steps)
+    rows += [(gen.ROPE, j, 3 + j % 50, 8, 128, 0, 0) for j in range(n_steps) for _ in range(20)]
+    rows += [(gen.ROPE, n_steps + i, 3 + i % 5, 8, 128, 0, 0) for i in range(2000)]
+    wl = gen.Workload("bad", make_desc(rows, [[(1 + j % 7, 5)] for j in range(n_steps)]), steprec(n_steps),
+                      gen.specs_grid(200, 5), gen.make_heads(16, 128, "bf16"), gen.HostConsts())
+    ref, st, _ = _steps(wl, False, True)
+    assert st == abi.KS_EINVAL
+    got, st, seen = _steps(wl, True, True)
+    assert st == abi.KS_EINVAL and seen == [gen.ROPE]
+    np.testing.assert_array_equal(got["t_kernel"], ref["t_kernel"])
+    for k in ("t_body", "t_gpu", "t_step"):   # fp32 within 64-record tiles: 6 levels of adds
+        np.testing.assert_allclose(got[k], ref[k], rtol=6 * 2.0 ** -24)
