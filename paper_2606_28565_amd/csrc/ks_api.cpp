@@ -60,7 +60,7 @@ constexpr size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // and, where the different records are evaluated instead of all (uniq_plan):
 //   ctl     : 256 B, right after range (cleared with it): their count per
 //             family [KS_NFAM] and, from word 16, a flag per family that they
-//             did not fit
+//             did not fit, and one that some family's did not
 //   rows    : uint32 per table slot: a record's row + 1 (cleared with range)
 //   slot    : uint32 per table slot, after carry: its index
 //   count   : uint32 per chunk: its entries

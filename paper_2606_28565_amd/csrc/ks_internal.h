@@ -76,7 +76,8 @@ struct UniqParams {
   UniqEntry *ent;
   uint32_t *dir;        // [KS_NFAM][n_steps][2]: first entry + 1, end row (zero: no such records)
   uint32_t *list, *count;
-  uint32_t *over;          // [KS_NFAM] nonzero: a family's did not fit, all its records are evaluated
+  uint32_t *over;          // [KS_NFAM + 1] nonzero: a family's did not fit, all its records are evaluated; last: some
+                           // family's
   uint32_t *chunk_count;   // entries of each chunk
   uint32_t *slot_row;      // a slot's record: row + 1, or 0
   uint32_t *slot_id;       // ... and its index among the different records

@@ -1490,8 +1490,9 @@ struct UniqTiles {
 // took 5 to 10 us, with its divisions in a row).
 __device__ __forceinline__ void uniq_tiles(const EvalParams &p, int grid, UniqTiles &u) {
   const int lane = threadIdx.x & 63, f = lane < KS_NFAM ? lane : 0;
-  const bool on = ((p.uniq_mask >> f) & 1u) && !p.u_over[f];
-  const int cnt = lane < KS_NFAM && on ? (int)min(p.u_count[f], p.u_cap[f]) : 0;
+  const uint32_t over = p.u_over[f], count = p.u_count[f];   // (in flight together)
+  const bool on = ((p.uniq_mask >> f) & 1u) && !over;
+  const int cnt = lane < KS_NFAM && on ? (int)min(count, p.u_cap[f]) : 0;
   const int t64 = (cnt + kTileRows - 1) / kTileRows;
   int rest = lane < KS_NFAM && !on ? p.wgt_off[f + 1] - p.wgt_off[f] : 0, tiles = t64, all = rest;
 #pragma unroll

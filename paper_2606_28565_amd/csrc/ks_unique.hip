@@ -91,6 +91,12 @@ __device__ __forceinline__ uint32_t slot_of(const UniqParams &p, int f, uint32_t
   return p.slot_off[f] + ((m + place) & p.slot_mask[f]);
 }
 
+// Family f's different records do not fit: all its records are evaluated.
+__device__ __forceinline__ void no_room(const UniqParams &p, int f) {
+  p.over[f] = 1u;
+  p.over[KS_NFAM] = 1u;
+}
+
 // What k_unique's passes share in LDS.
 struct UniqShared {
   uint32_t bad_of[kUniqChunk];        // per piece: bit q - 1, some record differs from the one q before; then its period
@@ -199,7 +205,7 @@ __global__ __launch_bounds__(kUqThreads) __attribute__((amdgpu_waves_per_eu(8)))
   }
   if (flag) {
     atomicOr(p.err, flag);
-    if (p.pair) p.over[f] = 1u;
+    if (p.pair) no_room(p, f);
   }
   uint32_t piece = 0;
   {
@@ -257,7 +263,7 @@ __global__ __launch_bounds__(kUqThreads) __attribute__((amdgpu_waves_per_eu(8)))
   // hang on which of the records that share a slot was stored last)
   const uint32_t slots = p.chunk_entries[f];
   if (n_ent > min(slots, 4u * n_pieces + p.spare[f])) {
-    if (tid == 0) p.over[f] = 1u;
+    if (tid == 0) no_room(p, f);
     return;
   }
   const uint32_t ent0 = p.ent_off[f] + (uint32_t)(c - p.chunk_off[f]) * slots;
@@ -318,7 +324,7 @@ __device__ __forceinline__ UniqKey key_of(const UniqParams &p, int f, uint32_t r
 // its records are evaluated).
 __device__ __forceinline__ uint32_t take_records(const UniqParams &p, int f, uint32_t n) {
   const uint32_t i = atomicAdd(p.count + f, n);
-  if (i + n > p.cap[f]) p.over[f] = 1u;
+  if (i + n > p.cap[f]) no_room(p, f);
   return i;
 }
 

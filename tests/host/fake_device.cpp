@@ -130,7 +130,7 @@ hipError_t launch_eval(int, const EvalParams &p, hipStream_t) {
     }
     if (!p.range) fill(u.dir, 2 * KS_NFAM * J);
     fill(u.count, KS_NFAM);
-    fill(u.over, KS_NFAM);
+    fill(u.over, KS_NFAM + 1);
     fill(u.chunk_count, chunks);
     fill(u.list, records);
     fill(u.slot_row, slots);
