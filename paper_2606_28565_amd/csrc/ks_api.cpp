@@ -397,7 +397,8 @@ void fill_eval(ks::EvalParams &p, const ks_desc *d, const ks_spec *specs, int32_
 // the direct evaluation of a grid.)
 bool takes_uniq(const ks_desc *d, int32_t n_specs, const ks_heads *h, int kind, const ks_kernel_out *kout,
                 size_t ws_bytes, UniqPlan *pl, Layout *L, bool *pair) {
-  if (kind == ks::kEtaOne || kind == ks::kBoundedOnly || d->n_rows == 0) return false;
+  if (kind == ks::kEtaOne || kind == ks::kBoundedOnly) return false;
+  if ((double)d->n_rows * n_specs * kUniqMost < kUniqSecs) return false;
   *pair = kout && (kout->t_roof || kout->eta || kout->t_kernel);
   if (kout && kout->source && h->grid_mask) return false;
   const double head = 2.0 * h->hidden * (h->in_dim + h->hidden) / head_rate(h);

@@ -1466,13 +1466,18 @@ __host__ __device__ inline uint32_t spec_cost(uint32_t tiles, uint32_t grid, uin
   return (tiles * ranges + grid - 1) / grid * (5 * per + 4);
 }
 
+// Tiles that fill the grid by themselves are split only for an eighth less: two
+// specs in two ranges (27 for 28) took 43 us where one range takes 35 (342 tiles on
+// 256 workgroups, bf16 32-256, GEMMs on the bounded head), sixteen in three (136
+// for 168) 172 and 202 (290 tiles, a collapsed mixture of experts).
 inline int spec_ranges(uint32_t tiles, uint32_t grid, uint32_t S) {
-  uint32_t best = 1, cost = ~0u;
+  uint32_t best = 1, cost = ~0u, whole = 0;
   for (uint32_t k = 0; k <= 4; ++k) {
     uint32_t c, t = spec_cost(tiles, grid, S, k, c);
+    if (k == 0) whole = t;
     if (t < cost) cost = t, best = c;
   }
-  return (int)best;
+  return tiles < grid || 8 * cost <= 7 * whole ? (int)best : 1;
 }
 
 // The work of the unique-record variant, formed on the device (the different
@@ -2641,7 +2646,7 @@ static hipError_t launch_grid(const EvalParams &p, hipStream_t s) {
   EvalParams q = p;
   q.spec_chunk = p.n_specs;
   q.n_chunks = 1;
-  if (n_wgt < cap && p.n_specs > 1) {
+  if (n_wgt < 4 * cap && p.n_specs > 1) {
     q.n_chunks = spec_ranges(n_wgt, cap, p.n_specs);
     q.spec_chunk = (p.n_specs + q.n_chunks - 1) / q.n_chunks;
   }

@@ -39,17 +39,17 @@ def test_request_sums_around_the_prologue_rule(n_steps, per_step, n_specs):
     assert g.rel_err(out["t_kernel"], t).max() <= 1e-5
 
 
-def _steps(wl, room, pairs=False):
+def _steps(wl, room, pairs=False, n_specs=None):
     """Step sums (and t_kernel), the device status and, with room, the families whose
     different records did not fit (a flag each, from word 16 after the record ranges)."""
     import torch
-    di = abi.DeviceInputs(wl)
+    di = abi.DeviceInputs(wl, n_specs=n_specs)
     up = lambda x: -(-x // 256) * 256
     S, N = wl.desc.n_steps, di.n_specs
     ctl = 256 + up(64 * N) + up(32 * S) + up(80 * S)
     tiles = sum(-(-int(k) // 64) for k in np.diff(wl.desc.fam_off))
     small = ctl + up(80 * N * S) + up(8 * N * tiles)
-    assert small < di.ws_bytes
+    assert not room or small < di.ws_bytes
     so_t, so = abi.step_outputs(S, N)
     ko_t, ko = abi.kernel_outputs(wl.desc.n_rows, N, counts=False, t_roof=False, eta=False) if pairs else ({}, None)
     abi.ks_eval_steps(di.desc, di.steps, di.specs_ptr, N, di.heads, di.host, so, ko, di.ws_ptr,
@@ -116,3 +116,21 @@ def test_bad_steps_of_one_family_with_per_pair_outputs():
     np.testing.assert_array_equal(got["t_kernel"], ref["t_kernel"])
     for k in ("t_body", "t_gpu", "t_step"):   # fp32 within 64-record tiles: 6 levels of adds
         np.testing.assert_allclose(got[k], ref[k], rtol=6 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("precision,in_dim,hidden", [("f32", 32, 128), ("bf16", 32, 256), ("bf16", 16, 64)])
+@pytest.mark.parametrize("tiles", [250, 290, 700, 1100])
+def test_spec_ranges_of_tiles_that_fill_the_grid(precision, in_dim, hidden, tiles):
+    """Every record evaluated, the spec vectors in one range or several: a spec's
+    outputs are those of a call with that spec alone, bit for bit."""
+    n_steps = tiles * 256 // 32
+    rows = [(gen.SILU_MUL, j, 1 + j % 900, 64 * (1 + i % 3), 0, 0, 0) for j in range(n_steps) for i in range(32)]
+    wl = gen.Workload("ranges", make_desc(rows, [[(1, 5)]] * n_steps), steprec(n_steps), gen.specs_grid(16, 5),
+                      gen.make_heads(in_dim, hidden, precision), gen.HostConsts())
+    got, st, _ = _steps(wl, False, True)
+    one, _, _ = _steps(wl, False, True, n_specs=1)
+    two, _, _ = _steps(wl, False, True, n_specs=2)
+    assert st == abi.KS_OK
+    for k in got:
+        np.testing.assert_array_equal(got[k][:1], one[k])
+        np.testing.assert_array_equal(got[k][:2], two[k])
