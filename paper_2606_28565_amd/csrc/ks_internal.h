@@ -42,7 +42,8 @@ struct alignas(16) SpecC {
   double rcp_nd;
   uint32_t n;
   float lr;  // log2(BW / P)
-  uint32_t pad[4];
+  uint32_t usual;  // the features of every record are below 2^5 (P and BW in 1 .. 2^100, an L2 size)
+  uint32_t pad[3];
 };
 static_assert(sizeof(SpecC) == 64, "SpecC is one 64-byte record");
 

@@ -325,6 +325,10 @@ __device__ void spec_prep_one(const ks_spec *__restrict__ specs, int s, SpecC *_
   c.rcp_bw = (float)(1.0 / BW);
   c.bw_over_p = (float)(BW / P);
   c.lr = (float)log2(BW / P);
+  // t_roof is below 2^80 then (F u below 2^80, Bt below 2^63) and t_comp + t_mem,
+  // unless zero, above 2^-101: x1, x6 and x7 are finite and below 2^5 like the others,
+  // which come from whole numbers below 2^64 and ratios of them
+  c.usual = P >= 1.0 && P <= 0x1p100 && BW >= 1.0 && BW <= 0x1p100 && sp.l2_bytes >= 0.0 ? 1u : 0u;
   c.l2 = (float)sp.l2_bytes;
   c.t0 = (float)sp.t0;
   c.rcp_t0 = (float)(1.0 / fmax(sp.t0, 1e-9));
@@ -1142,8 +1146,25 @@ struct HeadF32 {
   static constexpr int OFF_B2 = OFF_W2 + W2_DW;
   static constexpr int OFF_W3 = OFF_B2 + B2_DW;
   static constexpr int OFF_B3 = OFF_W3 + W3_DW;
-  static constexpr int LDS_DW = OFF_B3 + 4;
+  static constexpr int OFF_WIDE = OFF_B3 + 4;
+  static constexpr int LDS_DW = OFF_WIDE + 4;
   static constexpr bool kMlp = true;
+
+  // The pieces hold |v| < 2^127.99 (above, the leading one rounds to infinity, and
+  // what is left of infinity is NaN), exactly from 2^-102 up (below, up to 2^-126 is
+  // lost).  They are taken for weights W1 and W2 below 2^52, or W1 below 2^-10 and
+  // W2 below 2^62, b2 below 2^126 and w3 below 2^10: with features below 2^5 (their
+  // squares below 2^10) and not below 2^-102, h1 then is below 2^67 (2^5) and
+  // h2 - b2 below 2^126, and what the pieces lose moves h2 by less than 2^-42 and z
+  // by less than 2^-25.  Other weights (infinities and NaN among them), and spec
+  // vectors that give larger features, go through mlp_f32.
+  static constexpr uint32_t kW12 = 0x59800000u;   // 2^52
+  static constexpr uint32_t kW2 = 0x5E800000u, kW1 = 0x3A800000u;   // 2^62, 2^-10
+  static constexpr uint32_t kB2 = 0x7E800000u, kW3 = 0x44800000u;   // 2^126, 2^10
+  static constexpr uint32_t kBig = 1, kBigW2 = 2, kLargeW2 = 4, kUsualW1 = 8;
+  __device__ static __forceinline__ uint32_t size_of(float v) {   // orders like |v|, NaN above all
+    return __builtin_bit_cast(uint32_t, v) & 0x7FFFFFFFu;
+  }
 
   // a pair of values as three packed pairs of pieces
   __device__ static __forceinline__ void split(float a, float b, uint32_t &p0, uint32_t &p1, uint32_t &p2) {
@@ -1156,33 +1177,143 @@ struct HeadF32 {
     p2 = pack_bf16(a, b);
   }
 
+  // one value of any size as three pieces that sum to it
+  __device__ static void split_wide(float v, uint32_t (&p)[3]) {
+    const uint32_t top = __builtin_bit_cast(uint32_t, v) & 0xFFFF0000u;
+    const bool finite = fabsf(v) < __builtin_inff();
+    const float rest = finite ? v - __builtin_bit_cast(float, top) : 0.0f;
+    p[0] = __builtin_isnan(v) ? 0x7FC0u : top >> 16;
+    p[1] = pack_bf16(rest, 0.0f) & 0xFFFFu;
+    p[2] = pack_bf16(rest - bf16_to_f32(p[1]), 0.0f) & 0xFFFFu;
+  }
+
+  // weights d, d + kWgThreads, ... of a layer's n fragments' (KC of a row of blocks,
+  // stride its inputs); returns the largest size_of.  WIDE: of any size.
+  template <bool WIDE, int KC, class K>
+  __device__ static __forceinline__ uint32_t stage_layer(uint32_t *lds, const float *w, int stride, int tid, K &&k0) {
+    uint32_t most = 0;
+    // (eight rounds' loads in flight, as in the bf16 head; both layers' counts are multiples)
+#pragma unroll WIDE ? 1 : 8
+    for (int i = 0; i < MB * KC * 256 / kWgThreads; ++i) {
+      const int d = tid + i * kWgThreads;
+      const int q = d & 3, lane = (d >> 2) & 63, frag = d >> 8;
+      const int kc = frag % KC, mb = frag / KC;
+      const float *v = w + (mb * 32 + (lane & 31)) * stride + k0(kc, (lane >> 5) * 8 + 2 * q);
+      uint32_t *o = lds + frag * kFrag + (d & 255);
+      if constexpr (WIDE) {
+        uint32_t a[3], b[3];
+        split_wide(v[0], a);
+        split_wide(v[1], b);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) o[256 * i] = a[i] | b[i] << 16;
+      } else {
+        split(v[0], v[1], o[0], o[256], o[512]);
+        most = max(most, max(size_of(v[0]), size_of(v[1])));
+      }
+    }
+    return most;
+  }
+
   __device__ static void stage(uint32_t *lds, int fam, const EvalParams &p) {
     const float *w1 = (const float *)p.w1 + (size_t)fam * HID * IN;
     const float *w2 = (const float *)p.w2 + (size_t)fam * HID * HID;
     const float *b2 = (const float *)p.b2 + (size_t)fam * HID;
     const float *w3 = (const float *)p.w3 + (size_t)fam * HID;
     float *f = (float *)lds;
-    for (int d = threadIdx.x; d < MB * KC1 * 256; d += kWgThreads) {
-      const int q = d & 3, lane = (d >> 2) & 63, frag = d >> 8;
-      const int kc = frag % KC1, mb = frag / KC1;
-      const float *w = w1 + (mb * 32 + (lane & 31)) * IN + kc * 16 + (lane >> 5) * 8 + 2 * q;
-      uint32_t *o = lds + frag * kFrag + (d & 255);
-      split(w[0], w[1], o[0], o[256], o[512]);
-    }
-    for (int d = threadIdx.x; d < MB * KC2 * 256; d += kWgThreads) {
-      const int q = d & 3, lane = (d >> 2) & 63, frag = d >> 8;
-      const int kc = frag % KC2, mb = frag / KC2;
-      // (hid_of of an even slot and the next are consecutive units)
-      const float *w = w2 + (mb * 32 + (lane & 31)) * HID + B::hid_of(kc, (lane >> 5) * 8 + 2 * q);
-      uint32_t *o = lds + OFF_W2 + frag * kFrag + (d & 255);
-      split(w[0], w[1], o[0], o[256], o[512]);
-    }
-    for (int d = threadIdx.x; d < B2_DW; d += kWgThreads) {
+    // (addresses formed here rather than kept across the work loop, as in the bf16 head)
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    uint32_t big = 0;
+    auto in1 = [](int kc, int slot) { return kc * 16 + slot; };
+    auto in2 = [](int kc, int slot) { return B::hid_of(kc, slot); };   // (of an even slot and the next: consecutive units)
+    const uint32_t m1 = stage_layer<false, KC1>(lds, w1, IN, tid, in1);
+    const uint32_t m2 = stage_layer<false, KC2>(lds + OFF_W2, w2, HID, tid, in2);
+    static_assert(B2_DW <= kWgThreads, "a thread per bias");
+    if (const int d = tid; d < B2_DW) {
       const int r = d & 15, g = (d >> 4) & 1, mb = d >> 5;
-      f[OFF_B2 + d] = b2[B::out_of(mb, g, r)];
-      f[OFF_W3 + d] = w3[B::out_of(mb, g, r)];
+      const float b = b2[B::out_of(mb, g, r)], w = w3[B::out_of(mb, g, r)];
+      f[OFF_B2 + d] = b;
+      f[OFF_W3 + d] = w;
+      if (size_of(b) >= kB2 || size_of(w) >= kW3) big = kBig;
     }
     if (threadIdx.x == 0) f[OFF_B3] = ((const float *)p.b3)[fam];
+    // (a word per wave, so that none is reset)
+    const uint32_t sizes = (__ballot(big != 0 || m1 >= kW12) ? kBig : 0u) | (__ballot(m2 >= kW2) ? kBigW2 : 0u) |
+                           (__ballot(m2 >= kW12) ? kLargeW2 : 0u) | (__ballot(m1 >= kW1) ? kUsualW1 : 0u);
+    if ((threadIdx.x & 63) == 0) lds[OFF_WIDE + (threadIdx.x >> 6)] = sizes;
+    if (max(m1, m2) >= kB2) {   // (a thread writes the same places)
+      stage_layer<true, KC1>(lds, w1, IN, tid, in1);
+      stage_layer<true, KC2>(lds + OFF_W2, w2, HID, tid, in2);
+    }
+  }
+
+  // whether the staged family's weights are beyond the pieces
+  __device__ static __forceinline__ bool wide_weights(const uint32_t *lds) {
+    const u32x4 w = *(const u32x4 *)(lds + OFF_WIDE);
+    const uint32_t sizes = __builtin_amdgcn_readfirstlane(w[0] | w[1] | w[2] | w[3]);
+    return (sizes & (kBig | kBigW2)) != 0 || (sizes & (kLargeW2 | kUsualW1)) == (kLargeW2 | kUsualW1);
+  }
+
+  // The head on the fp32 instruction, for weights and features of any size: a
+  // fragment's lane holds the operand's row l % 32 at the slots of its half, and so
+  // does each of the eight 32x32x2 products here (K = 2: one slot of either half).
+  __device__ static __forceinline__ void product_f32(const uint32_t *frag, int lane, const float (&b)[2][8],
+                                                     f32x16 (&c)[2]) {
+    const u32x4 a0 = *(const u32x4 *)(frag + lane * 4), a1 = *(const u32x4 *)(frag + 256 + lane * 4),
+                a2 = *(const u32x4 *)(frag + 512 + lane * 4);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int sh = j & 1 ? 0 : 16;
+      auto piece = [&](uint32_t v) { return __builtin_bit_cast(float, (v << sh) & 0xFFFF0000u); };
+      const float a = piece(a0[j >> 1]) + piece(a1[j >> 1]) + piece(a2[j >> 1]);
+      c[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b[0][j], c[0], 0, 0, 0);
+      c[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b[1][j], c[1], 0, 0, 0);
+    }
+  }
+
+  __device__ static __forceinline__ float mlp_f32(const float (&x)[IN], const uint32_t *lds) {
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));   // (its addresses formed here, not kept across the spec loop)
+    const int g = lane >> 5;
+    const float *f = (const float *)lds;
+    float X[KC1][2][8];
+#pragma unroll
+    for (int kc = 0; kc < KC1; ++kc)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        uint32_t lo = __builtin_bit_cast(uint32_t, x[16 * kc + j]), hi = __builtin_bit_cast(uint32_t, x[16 * kc + 8 + j]);
+        swap32(lo, hi);
+        X[kc][0][j] = __builtin_bit_cast(float, lo);
+        X[kc][1][j] = __builtin_bit_cast(float, hi);
+      }
+    float H[KC2][2][8];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      f32x16 c[2] = {f32x16{}, f32x16{}};
+#pragma unroll
+      for (int kc = 0; kc < KC1; ++kc) product_f32(lds + (mb * KC1 + kc) * kFrag, lane, X[kc], c);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) H[2 * mb + (r >> 3)][i][r & 7] = fmaxf(c[i][r], 0.0f);
+    }
+    float z[2] = {0.0f, 0.0f};
+#pragma unroll 1
+    for (int mb = 0; mb < MB; ++mb) {
+      const f32x16 bias = *(const f32x16 *)(f + OFF_B2 + (mb * 2 + g) * 16);
+      f32x16 c[2] = {bias, bias};
+#pragma unroll
+      for (int kc = 0; kc < KC2; ++kc) product_f32(lds + OFF_W2 + (mb * KC2 + kc) * kFrag, lane, H[kc], c);
+      const float *w3 = f + OFF_W3 + (mb * 2 + g) * 16;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        z[0] = fmaf(w3[r], fmaxf(c[0][r], 0.0f), z[0]);
+        z[1] = fmaf(w3[r], fmaxf(c[1][r], 0.0f), z[1]);
+      }
+    }
+    uint32_t a0 = __builtin_bit_cast(uint32_t, z[0]), a1 = __builtin_bit_cast(uint32_t, z[1]);
+    swap32(a0, a1);
+    return __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1) + f[OFF_B3];
   }
 
   // hi += a0 b0; lo += the five products below it; for the two column blocks
@@ -1445,6 +1576,10 @@ __device__ __forceinline__ void tile_edges(const Tile &t, const Fields &f, uint3
 // nothing is left out: 46 us with it, 39 without).
 enum : int { kVarGrid = 1, kVarMult = 2, kVarUniq = 4, kVarRest = 2, kNumVars = 8 };
 
+// heads with limits on their weights and features, beyond which they take mlp_f32
+template <class H, class = void> struct SizedOK : std::false_type {};
+template <class H> struct SizedOK<H, std::void_t<decltype(H::kW12)>> : std::true_type {};
+
 // heads that take the software-pipelined spec loop
 template <class H, class = void> struct PipeOK : std::false_type {};
 template <class H> struct PipeOK<H, std::enable_if_t<H::kPipe>> : std::true_type {};
@@ -1662,6 +1797,7 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
   // better overall)
   constexpr bool VEC = !H::kMlp || MinWg<KIND>::value == 1;
   int staged = -1;
+  bool wide_head = false;   // the staged family's weights
   // With few work items per workgroup the heads take a contiguous range of
   // them, so that a workgroup meets one or two families and stages their
   // weights into LDS once or twice (striding over the grid it restaged them
@@ -1734,6 +1870,7 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
         }
         __syncthreads();
         staged = fam;
+        if constexpr (SizedOK<H>::value) wide_head = !bnd && H::wide_weights(lds);
       }
     }
     if (tc.nvalid == 0) continue;
@@ -1898,8 +2035,15 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
         continue;
       }
     }
+    bool rest = false;   // some of the specs are beyond the pieces' limits
     for (int s = s_lo; s < s_hi; ++s) {
       const SpecC sc = spec_at(p.spec_c, s);
+      if constexpr (SizedOK<H>::value) {
+        if (!sc.usual || wide_head) {
+          rest = true;
+          continue;
+        }
+      }
       const Roof o = small ? roofline<true>(rc, sc) : roofline<false>(rc, sc);
       float eta = 1.0f;
       // Tier B first: the family's other head runs only if some record of
@@ -1932,6 +2076,32 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
         if (valid && p.o_src) p.o_src[(size_t)s * (size_t)p.fam_off[KS_NFAM] + (size_t)row] = routed ? 2 : (bnd ? 1 : 0);
       }
       spec_tail<MULT, UNIQ, REST>(p, s, o.t_roof, eta, t, valid, live, row, tfac, fac, dst, u_dst);
+    }
+    if constexpr (SizedOK<H>::value) {
+      // those, in a loop of their own that costs the others no registers
+      for (int s = s_lo; rest && s < s_hi; ++s) {
+        const SpecC sc = spec_at(p.spec_c, s);
+        if (sc.usual && !wide_head) continue;
+        const Roof o = small ? roofline<true>(rc, sc) : roofline<false>(rc, sc);
+        float x[IN], eta;
+        features<IN>(rc, sc, o, x);
+        if (bnd) {
+          float x16[16];
+          features<16>(rc, sc, o, x16);
+          eta = bounded_eta(x16, o.W, bnd_lds);
+        } else {
+          eta = 1.0f + __expf(-H::mlp_f32(x, lds));
+        }
+        bool routed = false;
+        float eta_g = 0.0f;
+        if (grd) eta_g = grid_eta(rc, sc, o, p, grid_lds, routed);
+        if (routed) eta = eta_g;
+        const float t = fmaxf(o.t_roof * eta, sc.t0);
+        if constexpr (GRID && !UNIQ) {
+          if (valid && p.o_src) p.o_src[(size_t)s * (size_t)p.fam_off[KS_NFAM] + (size_t)row] = routed ? 2 : (bnd ? 1 : 0);
+        }
+        spec_tail<MULT, UNIQ, REST>(p, s, o.t_roof, eta, t, valid, live, row, tfac, fac, dst, u_dst);
+      }
     }
   }
 }
