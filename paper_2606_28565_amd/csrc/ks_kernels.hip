@@ -1119,8 +1119,9 @@ struct HeadBF16 {
 // the fp32 one per cycle: every operand is split exactly into three bfloat16
 // pieces of 8 bits (x = x0 + x1 + x2, each the rest rounded to nearest), and of
 // the nine products of pieces the six down to 2^-17 of the whole are formed,
-// each exact in fp32.  What is left out is below 2^-26 of a product, a quarter
-// of the rounding of one fp32 product.  The leading products and the others
+// each exact in fp32.  What is left out (x1 y2 + x2 y1 + x2 y2, |x1| <= 2^-8 and
+// |x2| <= 2^-17 of the binade) is below 2^-24 of a product, the rounding of one
+// fp32 product.  The leading products and the others
 // are summed apart (fp32, in the instruction) and added at the end, so that
 // the leading sum is rounded once per 16 terms rather than once per 2: eta's
 // root mean square error against 64 bits went from 4.8e-8 to 4.7e-8 (16-128)

@@ -83,7 +83,7 @@ __device__ __forceinline__ uint32_t waves_before(const uint32_t *wave_sum, uint3
 
 // The slot of a record in its family's table: attention's is its step's, a
 // dense one's is its m off a place of its (n, k), so that the token counts of
-// one kernel never meet in a slot.
+// one kernel meet in a slot only a table's size apart.
 __device__ __forceinline__ uint32_t slot_of(const UniqParams &p, int f, uint32_t step, uint32_t m, uint32_t n,
                                             uint32_t k) {
   if (f == KS_ATTN_PREFILL || f == KS_ATTN_DECODE) return p.slot_off[f] + step;
