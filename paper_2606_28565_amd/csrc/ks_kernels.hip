@@ -1575,7 +1575,7 @@ __device__ __forceinline__ void tile_edges(const Tile &t, const Fields &f, uint3
 // different records did not fit): one launch, whose parts fill each other's last round
 // (MoE trace 61 -> 54 us), but the code of both (homogeneous 70B trace, where
 // nothing is left out: 46 us with it, 39 without).
-enum : int { kVarGrid = 1, kVarMult = 2, kVarUniq = 4, kVarRest = 2, kNumVars = 8 };
+enum : int { kVarGrid = 1, kVarMult = 2, kVarUniq = 4, kVarRest = 8, kNumVars = 16 };
 
 // heads with limits on their weights and features, beyond which they take mlp_f32
 template <class H, class = void> struct SizedOK : std::false_type {};
@@ -1772,7 +1772,7 @@ __global__ __launch_bounds__(kWgThreads, MinWg<KIND>::value) void k_eval(EvalPar
   constexpr bool GRID = (VAR & kVarGrid) != 0;
   constexpr bool UNIQ = (VAR & kVarUniq) != 0;
   constexpr bool REST = !UNIQ || (VAR & kVarRest) != 0;
-  constexpr bool MULT = (VAR & kVarMult) != 0;   // (kVarRest: if there are any)
+  constexpr bool MULT = (VAR & (kVarMult | kVarRest)) != 0;   // (kVarRest: if there are any)
   using H = typename KindOf<KIND>::H;
   constexpr int IN = KindOf<KIND>::IN;
   __shared__ __align__(16) uint32_t lds[H::LDS_DW];   // 16-byte fragment reads, 8-byte staging writes
