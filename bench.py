@@ -29,7 +29,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 METRIC = "kernel latency predictions/sec and step evals/sec at 1 GPU; % of HBM/MFMA peak"
-PEAK = {"bf16": 2.5e15, "f32": 157.3e12, "hbm": 8.0e12}
+# (fp32 heads: six products of bfloat16 pieces on the bf16 instruction for each of theirs)
+PEAK = {"bf16": 2.5e15, "f32": 2.5e15 / 6, "hbm": 8.0e12}
 
 
 C5_BATCH_STEPS = 88_640      # 88,640 steps x 722 kernels = 64.0 M records
@@ -163,25 +164,33 @@ def head_flops_per_pair(in_dim: int, hidden: int) -> int:
     return 2 * (in_dim * hidden + hidden * hidden + hidden)
 
 
-def different_records(t: dict, fam_off) -> int:
-    """How many records of a call differ in the fields their latency depends
-    on: the head evaluates each of them once for every spec vector, and the
-    call's predictions, one per record and spec vector, come from those.
-    Dense records by (m, n, k), attention by (step, n, k, a); grouped GEMMs
-    all (each has its own routed rows).  t: the record fields on the GPU."""
+def evaluated_records(t: dict, fam_off, taken: int, bounded: int = 0):
+    """How many records of a call are evaluated, and how many of those on the
+    MLP head (the families outside `bounded`).  In the families of `taken`
+    (ks_different_families) each record that differs in the fields its latency
+    depends on is, once for every spec vector, and the call's predictions, one
+    per record and spec vector, come from those: dense records differ by (m, n,
+    k), attention by (step, n, k, a).  In the others every record is.  t: the
+    record fields."""
     import torch
-    total = 0
+    total = on_mlp = 0
+
+    def add(f, n):
+        nonlocal total, on_mlp
+        total += n
+        on_mlp += 0 if (bounded >> f) & 1 else n
+
     for f in range(len(fam_off) - 1):
         lo, hi = int(fam_off[f]), int(fam_off[f + 1])
-        if f == 2 or hi - lo < 2:
-            total += hi - lo
+        if not (taken >> f) & 1 or hi - lo < 2:
+            add(f, hi - lo)
             continue
         x = {name: t[name][lo:hi].long() for name in ("step", "m", "n", "k", "a")}
         k = 0 if f in (5, 7, 9) else x["k"]      # RMSNorm, SiLU and embedding have no K
         key = ((x["step"] << 36) | (x["n"] << 24) | (k << 12) | x["a"]) if f in (3, 4) else \
             ((x["m"] << 36) | (x["n"] << 18) | k)
-        total += int(torch.unique(key).numel())
-    return total
+        add(f, int(torch.unique(key).numel()))
+    return total, on_mlp
 
 
 def host_threads() -> int:
@@ -553,7 +562,9 @@ def _bench_sweep(args) -> int:
         bound, unit, peak, dtype = "hbm", "GB/s", PEAK["hbm"] / 1e9, "f32"
         achieved = alg / (k_ms * 1e-3) / 1e9
     else:
-        eval_rows = sum(different_records((pt["db"] or pt["di"]).t, pt["desc"].fam_off) for pt in parts)
+        eval_rows = sum(evaluated_records((pt["db"] or pt["di"]).t, pt["desc"].fam_off,
+                                          abi.ks_different_families(pt["desc"], n_specs, pt["heads"], None,
+                                                                    pt["ws_bytes"]))[0] for pt in parts)
         alg = float(eval_rows) * n_specs * head_flops_per_pair(in_dim, hidden)
         bound, unit, peak, dtype = "mfma", "TFLOP/s", PEAK["bf16"] / 1e12, "bf16"
         achieved = alg / (k_ms * 1e-3) / 1e12
@@ -571,7 +582,7 @@ def _bench_sweep(args) -> int:
         "roofline": {"bound": bound, "achieved": achieved, "peak": peak, "unit": unit, "frac": achieved / peak,
                      "traffic": recorded_traffic(traffic_key(args)), "kernel_ms": k_ms,
                      "note": "achieved = algorithmic work of the sweep's evaluations (head FLOPs over the "
-                             "different records, or the bytes the model reads and writes) / "
+                             "evaluated records, or the bytes the model reads and writes) / "
                              "the sum of those kernels' mean durations from HIP events around each launch; "
                              "traffic = HBM bytes of those launches per sweep (counters)"},
         "calls": [{"name": pt["name"], "records": pt["rows"], "kernel_ms": pt["kernel_ms"],
@@ -869,13 +880,13 @@ def main() -> int:
         achieved = alg / (k_ms * 1e-3) / 1e9 if alg is not None else None
         dtype = "f32"
     else:
-        # the head's work is per different record; of those in the share of the
-        # pairs that are left to it (bounded families and grids take the others)
+        # the head's work is per evaluated record outside the bounded families, and
+        # with grids in the share of the pairs that is left to it
         per_pair = head_flops_per_pair(wl.heads.in_dim, wl.heads.hidden)
-        src = (db.t, db.fam_off) if db is not None else (di.t, wl.desc.fam_off)
-        different = different_records(*src)
-        alg = float(mlp_pairs) / n_eval * different * per_pair
-        n_eval = different
+        desc, t, ws_bytes = (db.desc, db.t, ews_bytes) if db is not None else (di.desc, di.t, di.ws_bytes)
+        taken = abi.ks_different_families(desc, di.n_specs, heads, ko, ws_bytes)
+        n_eval, n_mlp = evaluated_records(t, desc.fam_off, taken, bmask)
+        alg = float(n_mlp) * di.n_specs * mlp_pairs / (on_mlp_n * di.n_specs) * per_pair
         bf16 = wl.heads.precision == "bf16"
         bound, unit = "mfma", "TFLOP/s"
         peak = (PEAK["bf16"] if bf16 else PEAK["f32"]) / 1e12
@@ -904,10 +915,10 @@ def main() -> int:
                      "traffic": recorded_traffic(traffic_key(args)),
                      "kernel_ms": k_ms, "evaluated_records": n_eval,
                      "note": "achieved = algorithmic work of one evaluation (FLOPs of the head over the "
-                             "different records, each evaluated once per spec vector, or the bytes the "
+                             "evaluated records, once per spec vector, or the bytes the "
                              "model reads and writes) / the mean duration of its kernels (finding the "
                              "different records among them) from HIP events around them on the call's "
-                             "stream"},
+                             "stream; fp32 peak = bf16 peak / 6 products of pieces"},
     }
     if exp is not None:
         out["expand"] = exp

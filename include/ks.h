@@ -457,6 +457,14 @@ ks_status ks_device_status(const void* ws, size_t ws_bytes, hipStream_t stream);
  * (created with timing enabled, never destroyed by the library). */
 ks_status ks_set_timing_events(hipEvent_t before, hipEvent_t after);
 
+/* Host only: the families (bit f) of which a call with these arguments (kout
+ * NULL: step sums alone) evaluates each different record once, as its
+ * ks_workspace_bytes() describes; 0 if it evaluates every record, or on bad
+ * arguments.  (A family whose different records turn out not to fit is
+ * evaluated record by record all the same.) */
+uint32_t ks_different_families(const ks_desc* desc, int32_t n_specs, const ks_heads* heads,
+                               const ks_kernel_out* kout, size_t ws_bytes);
+
 /* Message of the last non-OK status returned on this thread. */
 const char* ks_last_error(void);
 

@@ -156,6 +156,9 @@ def load(path: str = LIB_PATH) -> C.CDLL:
     lib.ks_simulate.restype = C.c_int
     lib.ks_set_timing_events.argtypes = [P, P]
     lib.ks_set_timing_events.restype = C.c_int
+    lib.ks_different_families.argtypes = [C.POINTER(ks_desc), C.c_int32, C.POINTER(ks_heads), C.POINTER(ks_kernel_out),
+                                          C.c_size_t]
+    lib.ks_different_families.restype = C.c_uint32
     lib.ks_last_error.argtypes = []
     lib.ks_last_error.restype = C.c_char_p
     lib.ks_version.argtypes = []
@@ -241,6 +244,12 @@ def ks_simulate(model, specs_ptr, n_specs, heads, host, sched, requests, outs, w
                             C.byref(requests), outs if isinstance(outs, C.Array) else C.byref(outs),
                             ws_ptr, ws_bytes, stream)
     return _check(st) if check else st
+
+
+def ks_different_families(desc, n_specs, heads, kout, ws_bytes) -> int:
+    """The families of which this call evaluates the different records only."""
+    return load().ks_different_families(C.byref(desc), n_specs, C.byref(heads),
+                                        None if kout is None else C.byref(kout), ws_bytes)
 
 
 def ks_set_timing_events(before, after, check=True):

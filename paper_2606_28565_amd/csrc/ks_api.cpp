@@ -924,6 +924,17 @@ ks_status ks_set_timing_events(hipEvent_t before, hipEvent_t after) {
   return KS_OK;
 }
 
+uint32_t ks_different_families(const ks_desc *desc, int32_t n_specs, const ks_heads *heads, const ks_kernel_out *kout,
+                               size_t ws_bytes) {
+  if (check_desc(desc) != KS_OK || n_specs < 1 || n_specs > (1 << 20)) return 0;
+  int kind;
+  if (head_kind(heads, &kind) != KS_OK) return 0;
+  UniqPlan pl;
+  Layout L;
+  bool pair;
+  return takes_uniq(desc, n_specs, heads, kind, kout, ws_bytes, &pl, &L, &pair) ? pl.mask : 0;
+}
+
 const char *ks_last_error(void) { return g_err.c_str(); }
 
 const char *ks_version(void) { return "ks 0.1.0 (gfx950)"; }

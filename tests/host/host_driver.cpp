@@ -459,6 +459,7 @@ int run_route() {
                                   : ks_eval_steps(&d, &st, specs.data(), S, &h, &host, &sum, outs ? &ko : nullptr, ws, wsb,
                                                   nullptr);
     std::free(ws);
+    if (r == KS_OK && ks_different_families(&d, S, &h, outs ? &ko : nullptr, wsb) != ks::eval_seen.mask) return 3;
     std::printf("status %d uniq %d mask %u pair %d apart %d bytes %zu\n", (int)r, (int)ks::eval_seen.uniq,
                 ks::eval_seen.mask, (int)ks::eval_seen.pair, (int)ks::eval_seen.apart, wsb);
   }
