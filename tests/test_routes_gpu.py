@@ -134,3 +134,40 @@ def test_spec_ranges_of_tiles_that_fill_the_grid(precision, in_dim, hidden, tile
     for k in got:
         np.testing.assert_array_equal(got[k][:1], one[k])
         np.testing.assert_array_equal(got[k][:2], two[k])
+
+
+@pytest.mark.parametrize("precision,in_dim,hidden,n_specs", [("bf16", 16, 128, 400), ("bf16", 32, 256, 120), ("f32", 32, 128, 120)])
+def test_collapsed_mixture_of_experts(precision, in_dim, hidden, n_specs):
+    """A mixture of experts with its layers collapsed: one record of multiplicity 16
+    per layer-identical kernel, the grouped GEMMs one per layer, evaluated every one
+    beside the different ones of the rest (fp32 sums within 64-record tiles: 6
+    2^-24)."""
+    rng = np.random.Generator(np.random.PCG64(12))
+    L, n_steps, rows, experts = 16, 420, [], []
+    for j in range(n_steps):
+        m = int(rng.integers(1, 40))
+        for n in (6144, 4096, 8):
+            rows.append((gen.GEMM, j, m, n, 4096, 0, 0))
+        for _ in range(L):
+            for n, k in ((28672, 4096), (4096, 14336)):
+                rows.append((gen.GROUPED_GEMM, j, 0, n, k, 8, len(experts)))
+            experts += [int(x) for x in rng.integers(0, 12, 8)]
+        rows += [(gen.RMSNORM, j, m, 4096, 0, 0, 0)] * 2 + [(gen.SILU_MUL, j, 2 * m, 14336, 0, 0, 0),
+                                                            (gen.ATTN_DECODE, j, 0, 32, 128, 8, 0),
+                                                            (gen.LM_HEAD, j, m, 32000, 4096, 0, 0)]
+    d = make_desc(rows, [[(1, int(h)) for h in rng.integers(0, 4000, 3)] for _ in range(n_steps)], experts)
+    d.mult = np.where(np.isin(d.family(), (gen.GROUPED_GEMM, gen.LM_HEAD)), 1, L).astype(np.uint32)
+    wl = gen.Workload("moe", d, steprec(n_steps, layers=L, hidden=4096, tp=2), gen.specs_grid(n_specs, 5),
+                      gen.make_heads(in_dim, hidden, precision), gen.HostConsts())
+    di = abi.DeviceInputs(wl)
+    taken = abi.ks_different_families(di.desc, n_specs, di.heads, None, di.ws_bytes)
+    assert taken == sum(1 << f for f in np.unique(d.family()) if f != gen.GROUPED_GEMM)
+    ref, _, _ = _steps(wl, False, True)
+    got, st, seen = _steps(wl, True)
+    assert st == abi.KS_OK and seen == []
+    w = d.mult.astype(np.float64)
+    for s in range(n_specs):
+        body = np.bincount(d.step, weights=ref["t_kernel"][s].astype(np.float64) * w, minlength=n_steps)
+        np.testing.assert_allclose(got["t_body"][s], body, rtol=6 * 2.0 ** -24)
+    for k in ("t_gpu", "t_step"):
+        np.testing.assert_allclose(got[k], ref[k], rtol=12 * 2.0 ** -24)
