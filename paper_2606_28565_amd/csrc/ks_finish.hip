@@ -175,8 +175,9 @@ __device__ __forceinline__ void uniq_entries(const FinishParams &p, int f, uint3
 // Up to kFewSpecs spec vectors: a thread per step and family walks the family's
 // entries (the chain of dependent loads, directory, entry, slot, t, once for
 // all the tile's families) and sums every spec; then a thread per step and spec
-// adds the families in order.  (A thread per step and spec that walked the ten
-// families one after the other: 20 to 26 us where this takes 8.)  NS: the spec
+// adds the families in order: 8.6 us for 8000 steps (a thread per step and spec that
+// walked the ten families one after the other took 20 to 26), 12.9 for 20,000, 20
+// for 40,000 with a record per layer and 25 for 80,000 collapsed.  NS: the spec
 // count rounded up to a power of two.
 constexpr int kFewSpecs = 4;
 constexpr int kFewSteps = 16;

@@ -1127,11 +1127,11 @@ struct HeadBF16 {
 // root mean square error against 64 bits went from 4.8e-8 to 4.7e-8 (16-128)
 // and from 4.6e-8 to 4.2e-8 (32-128), its largest from 2.1e-7 to 1.2e-7.
 // 480 instructions of 32 cycles per wave and spec (32-128) instead of 640 of
-// 64: 704k pairs 303 -> 167 us, of which the matrix core is busy 60%, as in the
-// bf16 heads (running the split of one block under the products of the next,
-// by the compiler's group barriers or by hand, gave 167 to 177 us: the clock
-// under this load is 1.8 GHz).  Orientation, lane layout and hidden-unit order
-// are the bf16 head's.
+// 64: the fp32 grid's 704k pairs 303 -> 161 us, the matrix cores busy 51% of the
+// cycles by the counters, launch and staging among them (running the split of one
+// block under the products of the next, by the compiler's group barriers or by
+// hand, gave nothing).  Orientation, lane layout and hidden-unit order are the
+// bf16 head's.
 template <int IN, int HID>
 struct HeadF32 {
   static constexpr bool kRaw = false;
@@ -1574,7 +1574,8 @@ __device__ __forceinline__ void tile_edges(const Tile &t, const Fields &f, uint3
 // every record of the families left out (grouped GEMMs, and those whose
 // different records did not fit): one launch, whose parts fill each other's last round
 // (MoE trace 61 -> 54 us), but the code of both (homogeneous 70B trace, where
-// nothing is left out: 46 us with it, 39 without).
+// nothing is left out: 46 us with it, 39 without; 16 specs of a 7B trace whose
+// records do not repeat, 880 us of head work, 3% in all).
 enum : int { kVarGrid = 1, kVarMult = 2, kVarUniq = 4, kVarRest = 8, kNumVars = 16 };
 
 // heads with limits on their weights and features, beyond which they take mlp_f32

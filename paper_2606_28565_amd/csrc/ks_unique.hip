@@ -133,8 +133,8 @@ __device__ __forceinline__ void chunk_entry(const UniqParams &p, const UniqShare
 
 // Bound by the stream of records with eight workgroups per CU resident (a chunk
 // is a chain of four barriers and two memory round trips, some 6 us): 28.9M
-// records of a 70B batch in 110 us (4.1 TB/s of the fields read; loads alone 75),
-// 7.2M in 35.
+// records of a 70B batch in 114 us (491 MB read and 71 written by the counters,
+// 4.9 TB/s), 7.2M in 37, 390,000 in 8.
 __global__ __launch_bounds__(kUqThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_unique(UniqParams p, int n_agg) {
   __shared__ __align__(16) UniqShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -332,7 +332,8 @@ __device__ __forceinline__ uint32_t take_records(const UniqParams &p, int f, uin
 // listed (one atomic addition per workgroup).  The others: entries, by one wave
 // a quarter of a chunk with 1024 entry slots, else four chunks at 16 lanes each
 // (with a record per layer a chunk has 10 to 50 entries: a wave per chunk took
-// 26 us on the 70B batch where this takes 21).
+// 26 us on the 70B batch where four took 21; with four entries a lane in flight
+// 19.6, and 11.4 for 15.2 on the collapsed 70B trace).
 __global__ __launch_bounds__(kUqThreads) void k_join(UniqParams p) {
   __shared__ uint32_t wave_sum[kUqThreads / 64], first;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
